@@ -2,7 +2,7 @@
 // (Eq. 4) and the choice of the T most salient channels over all layers (Alg. 1).
 // Offline, off the timed path of the linear; the salience kernel is a plain streaming
 // reduction over W and G (4 bytes per weight), the selection a radix select over the
-// saliences' bit patterns followed by an ordered compaction per layer.
+// saliences' bit patterns followed by an ordered compaction.
 #include <algorithm>
 
 #include "internal.h"
@@ -64,108 +64,42 @@ __global__ __launch_bounds__(256) void channel_salience_kernel(const half_t *__r
 }
 
 // ---- global selection -------------------------------------------------------------------
-// Saliences are non-negative floats, so their bit patterns order like the values.  Four
-// passes of 256-bin histograms (most significant byte first) find the bit pattern of the
-// T-th largest salience and how many channels with exactly that value still belong to the
-// chosen set; equal values are taken in the order of the concatenation (earlier layer, then
-// lower channel).
+// Saliences are non-negative floats, so their bit patterns order like the values.  Three
+// histogram passes over digits of 11, 11 and 10 bits (most significant first) find the bit pattern
+// of the T-th largest salience and how many channels with exactly that value still belong to the
+// chosen set; equal values are taken in the order of the concatenation (earlier layer, then lower
+// channel).  The keys of a whole model are a megabyte or two: what bounds the selection is the
+// number of dependent launches and, inside one, atomics on the same global address (one per block
+// and occupied bin, about 20 ns each: the first pass of 1344 blocks of 256 threads took 28 us for
+// 344064 keys).  So the blocks are few and large, every block works out the previous pass's digit
+// for itself from the finished histogram instead of a launch of one thread doing so (4-9 us each),
+// and the lists are written from the ranks that tiles of the CONCATENATION have - a block per layer
+// walking its channels in order took 32 us to count and 117 us to write.  Seven launches where there were
+// thirteen; the search over 32 layers of 344064 channels with two gradient samples of a 4096 x 28672
+// layer (2 x 78 us of salience kernels) went from 493 to 262 us.
 
-struct SelectState {
-    uint32_t prefix;      // bytes of the threshold found so far
-    uint32_t remaining;   // rank still to be found inside the current prefix; after the last pass:
+constexpr int SEL_THREADS = 1024;
+constexpr int SEL_PASSES = 3;
+constexpr int SEL_BINS = 2048;        // 11 bits; the last digit has 10 and uses the lower half
+constexpr int SEL_OFFSETS = 1024;     // layer offsets the emitting block keeps in LDS
+constexpr int SEL_MAX_TILES = 1024;   // tiles of the concatenation: one per thread of the block that adds up their counts
+
+// digit of a pass: bits [shift, shift + width)
+__host__ __device__ constexpr int sel_shift(int pass) { return pass == 0 ? 21 : pass == 1 ? 10 : 0; }
+__host__ __device__ constexpr uint32_t sel_mask(int pass) { return pass == 2 ? 1023u : 2047u; }
+
+struct SelectRank {
+    uint32_t prefix;      // digits of the threshold found so far
+    uint32_t remaining;   // rank still to be found among the keys with that prefix; after the last pass:
                           // number of channels equal to the threshold that are chosen
-    uint32_t hist[256];
+};
+struct SelectState {
+    SelectRank rank[SEL_PASSES + 1];   // [i]: before pass i.  Written by one block of the launch after that pass
+    uint32_t hist[SEL_PASSES][SEL_BINS];
+    uint32_t tile_gt[SEL_MAX_TILES], tile_eq[SEL_MAX_TILES];
 };
 
-__global__ void select_init_kernel(SelectState *st, uint32_t T)
-{
-    const int t = threadIdx.x;
-    if (t < 256) st->hist[t] = 0;
-    if (t == 0) {
-        st->prefix = 0;
-        st->remaining = T;
-    }
-}
-
-// histogram of byte `pass` over the keys whose higher bytes equal the prefix
-__global__ __launch_bounds__(256) void select_hist_kernel(const uint32_t *__restrict__ keys, int64_t total, int pass, SelectState *st)
-{
-    __shared__ uint32_t h[256];
-    h[threadIdx.x] = 0;
-    __syncthreads();
-    const uint32_t prefix = st->prefix;
-    const int hi_shift = 8 * (pass + 1);
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-        const uint32_t k = keys[i];
-        const bool match = pass == 3 || (k >> hi_shift) == (prefix >> hi_shift);
-        if (match) atomicAdd(&h[(k >> (8 * pass)) & 255u], 1u);
-    }
-    __syncthreads();
-    if (h[threadIdx.x]) atomicAdd(&st->hist[threadIdx.x], h[threadIdx.x]);
-}
-
-// walk the bins from the largest byte value down to the one that holds the wanted rank
-__global__ void select_pick_kernel(SelectState *st, int pass)
-{
-    if (threadIdx.x == 0) {
-        uint32_t remaining = st->remaining;
-        int d = 255;
-        if (remaining > 0) {
-            while (d > 0 && st->hist[d] < remaining) {
-                remaining -= st->hist[d];
-                --d;
-            }
-            st->prefix |= (uint32_t)d << (8 * pass);
-            st->remaining = remaining;
-        } else {
-            st->prefix = 0xFFFFFFFFu;   // T = 0: nothing reaches the threshold
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x < 256) st->hist[threadIdx.x] = 0;
-}
-
-// per layer: channels above the threshold, channels equal to it
-__global__ __launch_bounds__(256) void select_count_kernel(const uint32_t *__restrict__ keys, const int64_t *__restrict__ offsets,
-                                                           const SelectState *st, uint32_t *gt, uint32_t *eq)
-{
-    __shared__ uint32_t s_gt, s_eq;
-    if (threadIdx.x == 0) s_gt = s_eq = 0;
-    __syncthreads();
-    const int l = blockIdx.x;
-    const uint32_t thr = st->prefix;
-    uint32_t a = 0, b = 0;
-    for (int64_t i = offsets[l] + threadIdx.x; i < offsets[l + 1]; i += 256) {
-        const uint32_t k = keys[i];
-        a += k > thr;
-        b += k == thr;
-    }
-    atomicAdd(&s_gt, a);
-    atomicAdd(&s_eq, b);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        gt[l] = s_gt;
-        eq[l] = s_eq;
-    }
-}
-
-// in layer order: how many of a layer's threshold-valued channels are chosen, where its list starts
-__global__ void select_scan_kernel(const SelectState *st, int L, const uint32_t *gt, const uint32_t *eq, uint32_t *eq_take,
-                                   uint32_t *out_off, int32_t *layer_counts)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    uint32_t left = st->prefix == 0xFFFFFFFFu ? 0u : st->remaining, run = 0;
-    for (int l = 0; l < L; ++l) {
-        const uint32_t take = eq[l] < left ? eq[l] : left;
-        left -= take;
-        eq_take[l] = take;
-        out_off[l] = run;
-        layer_counts[l] = (int32_t)(gt[l] + take);
-        run += gt[l] + take;
-    }
-}
-
-// exclusive prefix sum of one value per thread over the block of 256 (wave scans, then the 4 wave totals)
+// exclusive prefix sum of one value per thread over a block of 1024 (wave scans, then the 16 wave totals)
 __device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t *wave_tot, uint32_t &block_total)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -178,33 +112,162 @@ __device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t *wave_tot, 
     __syncthreads();   // wave_tot may still be read from the previous call
     if (lane == 63) wave_tot[wave] = inc;
     __syncthreads();
-    uint32_t base = 0;
-    for (int w = 0; w < wave; ++w) base += wave_tot[w];
-    block_total = wave_tot[0] + wave_tot[1] + wave_tot[2] + wave_tot[3];
+    uint32_t base = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < SEL_THREADS / 64; ++w) {
+        const uint32_t t = wave_tot[w];
+        base += w < wave ? t : 0u;
+        total += t;
+    }
+    block_total = total;
     return base + inc - v;
 }
 
-// one block per layer walks its channels in order and writes the chosen indices, ascending
-__global__ __launch_bounds__(256) void select_emit_kernel(const uint32_t *__restrict__ keys, const int64_t *__restrict__ offsets,
-                                                          const SelectState *st, const uint32_t *eq_take, const uint32_t *out_off,
-                                                          int32_t *selected)
+// The rank after pass `pass`, from its finished histogram: the largest digit with at least `remaining`
+// keys at or above it.  Every block computes it (thread t looks at the t-th pair of bins from the top);
+// block 0 leaves it for the next launch.
+__device__ inline SelectRank pick_digit(SelectState *st, int pass, uint32_t *wave_tot, SelectRank *found)
 {
-    __shared__ uint32_t wave_tot[4];
-    const int l = blockIdx.x;
-    const uint32_t thr = st->prefix, take = eq_take[l];
-    const int64_t lo = offsets[l], n = offsets[l + 1] - lo;
-    uint32_t eq_seen = 0, written = 0;
-    for (int64_t c0 = 0; c0 < n; c0 += 256) {
-        const int64_t c = c0 + threadIdx.x;
-        const uint32_t k = c < n ? keys[lo + c] : 0u;
-        const uint32_t is_eq = (c < n && k == thr) ? 1u : 0u;
-        uint32_t eq_total, sel_total;
-        const uint32_t eq_rank = eq_seen + block_exclusive_scan(is_eq, wave_tot, eq_total);
-        const uint32_t sel = (c < n && (k > thr || (is_eq && eq_rank < take))) ? 1u : 0u;
-        const uint32_t pos = written + block_exclusive_scan(sel, wave_tot, sel_total);
-        if (sel) selected[out_off[l] + pos] = (int32_t)c;
-        eq_seen += eq_total;
-        written += sel_total;
+    const SelectRank r = st->rank[pass];
+    const int d = SEL_BINS - 1 - 2 * (int)threadIdx.x;
+    const uint32_t hi = st->hist[pass][d], lo = st->hist[pass][d - 1];
+    if (threadIdx.x == 0) *found = r;
+    uint32_t total;
+    const uint32_t above = block_exclusive_scan(hi + lo, wave_tot, total);   // keys with a digit above d (its barriers order *found)
+    if (above < r.remaining && r.remaining <= above + hi + lo) {             // true in one thread
+        const bool upper = r.remaining <= above + hi;
+        found->prefix = r.prefix | ((uint32_t)(upper ? d : d - 1) << sel_shift(pass));
+        found->remaining = r.remaining - above - (upper ? 0u : hi);
+    }
+    __syncthreads();
+    const SelectRank out = *found;
+    if (blockIdx.x == 0 && threadIdx.x == 0) st->rank[pass + 1] = out;
+    return out;
+}
+
+// clears the counters and starts the ranks; the layers' counts start at zero
+__global__ __launch_bounds__(256) void select_init_kernel(SelectState *st, uint32_t T, int32_t *layer_counts, int L)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < SEL_PASSES * SEL_BINS) (&st->hist[0][0])[i] = 0;
+    if (i == 0) st->rank[0] = SelectRank{0, T};
+    for (int l = i; l < L; l += gridDim.x * 256) layer_counts[l] = 0;
+}
+
+// histogram of digit PASS over the keys whose higher digits equal the prefix
+template <int PASS>
+__global__ __launch_bounds__(SEL_THREADS) void select_hist_kernel(const uint32_t *__restrict__ keys, int64_t total, SelectState *st)
+{
+    __shared__ uint32_t h[SEL_BINS];
+    __shared__ uint32_t wave_tot[SEL_THREADS / 64];
+    __shared__ SelectRank found;
+    h[threadIdx.x] = 0;
+    h[threadIdx.x + SEL_THREADS] = 0;
+    uint32_t prefix = 0;
+    if constexpr (PASS > 0) prefix = pick_digit(st, PASS - 1, wave_tot, &found).prefix;
+    __syncthreads();
+    constexpr int above = PASS == 0 ? 31 : sel_shift(PASS > 0 ? PASS - 1 : 0);
+    for (int64_t i = (int64_t)blockIdx.x * SEL_THREADS + threadIdx.x; i < total; i += (int64_t)gridDim.x * SEL_THREADS) {
+        const uint32_t k = keys[i];
+        if (PASS == 0 || (k >> above) == (prefix >> above)) atomicAdd(&h[(k >> sel_shift(PASS)) & sel_mask(PASS)], 1u);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int d = threadIdx.x + j * SEL_THREADS;
+        if (h[d]) atomicAdd(&st->hist[PASS][d], h[d]);
+    }
+}
+
+// per tile of the concatenation: channels above the threshold, channels equal to it
+__global__ __launch_bounds__(SEL_THREADS) void select_count_kernel(const uint32_t *__restrict__ keys, int64_t total, int tile, SelectState *st)
+{
+    __shared__ uint32_t wave_tot[SEL_THREADS / 64];
+    __shared__ SelectRank found;
+    __shared__ uint32_t s_gt, s_eq;
+    const uint32_t thr = pick_digit(st, SEL_PASSES - 1, wave_tot, &found).prefix;
+    if (threadIdx.x == 0) s_gt = s_eq = 0;
+    __syncthreads();
+    const int64_t lo = (int64_t)blockIdx.x * tile, hi = min(lo + tile, total);
+    uint32_t a = 0, b = 0;
+    for (int64_t i = lo + threadIdx.x; i < hi; i += SEL_THREADS) {
+        const uint32_t k = keys[i];
+        a += k > thr;
+        b += k == thr;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        a += __shfl_xor(a, o, 64);
+        b += __shfl_xor(b, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicAdd(&s_gt, a);
+        atomicAdd(&s_eq, b);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        st->tile_gt[blockIdx.x] = s_gt;
+        st->tile_eq[blockIdx.x] = s_eq;
+    }
+}
+
+// Layers and their channels are consecutive in the concatenation, so a chosen channel's place in
+// `selected` is the number of chosen ones before it: those above the threshold, and of those equal to
+// it the first `remaining`.  A tile's start comes from the counts of the tiles before it.
+__global__ __launch_bounds__(SEL_THREADS) void select_emit_kernel(const uint32_t *__restrict__ keys, int64_t total, int tile,
+                                                                  const int64_t *__restrict__ offsets, int L, const SelectState *st,
+                                                                  int32_t *__restrict__ selected, int32_t *__restrict__ layer_counts)
+{
+    __shared__ uint32_t wave_tot[SEL_THREADS / 64];
+    __shared__ int64_t s_off[SEL_OFFSETS];
+    const int tid = threadIdx.x, lane = tid & 63;
+    // the search for a channel's layer is a chain of dependent reads: from LDS unless there are very many layers
+    const bool in_lds = L < SEL_OFFSETS;
+    if (in_lds && tid <= L) s_off[tid] = offsets[tid];
+    auto layer_of = [&](int64_t c) {   // the last layer that starts at or before c (an empty one starts where the next does)
+        int l = 0, r = L;              // offset of l <= c < offset of r
+        while (r - l > 1) {
+            const int m = (l + r) >> 1;
+            if ((in_lds ? s_off[m] : offsets[m]) <= c) l = m;
+            else r = m;
+        }
+        return l;
+    };
+    const uint32_t thr = st->rank[SEL_PASSES].prefix, take = st->rank[SEL_PASSES].remaining;
+    uint32_t gt_seen, eq_seen;
+    block_exclusive_scan(tid < (int)blockIdx.x ? st->tile_gt[tid] : 0u, wave_tot, gt_seen);
+    block_exclusive_scan(tid < (int)blockIdx.x ? st->tile_eq[tid] : 0u, wave_tot, eq_seen);
+    uint32_t written = gt_seen + min(eq_seen, take);
+    const int64_t lo = (int64_t)blockIdx.x * tile, hi = min(lo + tile, total);
+    for (int64_t c0 = lo; c0 < hi; c0 += SEL_THREADS) {
+        const int64_t c = c0 + tid;
+        const uint32_t k = c < hi ? keys[c] : 0u;
+        const uint32_t is_eq = (c < hi && k == thr) ? 1u : 0u;
+        // both counts of a chunk fit 16 bits: one scan finds them together
+        const uint32_t is_gt = (c < hi && k > thr) ? 1u : 0u;
+        uint32_t chunk;
+        const uint32_t before = block_exclusive_scan(is_gt | (is_eq << 16), wave_tot, chunk);
+        const uint32_t eq_rank = eq_seen + (before >> 16);
+        const bool sel = is_gt || (is_eq && eq_rank < take);
+        const uint32_t eq_here = min(eq_rank, take) - min(eq_seen, take);   // chosen equal ones of this chunk before this key
+        const int first_l = layer_of(c0), last_l = layer_of(min(c0 + SEL_THREADS, hi) - 1);
+        const uint32_t chosen = (chunk & 0xffffu) + min(eq_seen + (chunk >> 16), take) - min(eq_seen, take);
+        const int l = first_l == last_l ? first_l : layer_of(min(c, hi - 1));
+        if (sel) selected[written + (before & 0xffffu) + eq_here] = (int32_t)(c - (in_lds ? s_off[l] : offsets[l]));
+        // how many of each layer: one addition where the whole chunk is one layer's (every wave of a wide
+        // layer adding to its one address would queue up there), else one per wave and layer in it
+        if (first_l == last_l) {
+            if (tid == 0 && chosen) atomicAdd(&layer_counts[first_l], (int32_t)chosen);
+        } else {
+            for (uint64_t left = __ballot(sel); left;) {
+                const int of = __shfl(l, __ffsll((unsigned long long)left) - 1, 64);
+                const uint64_t same = __ballot(sel && l == of) & left;
+                if (lane == 0) atomicAdd(&layer_counts[of], (int32_t)__popcll(same));
+                left &= ~same;
+            }
+        }
+        written += chosen;
+        eq_seen += chunk >> 16;
     }
 }
 
@@ -234,22 +297,17 @@ int launch_channel_salience(const void *W, const void *Gr, int N, int K, float w
 
 size_t select_salient_workspace_bytes(int L)
 {
-    return align_up(sizeof(SelectState), 256) + align_up(sizeof(int64_t) * (size_t)(L + 1), 256) +
-           4 * align_up(sizeof(uint32_t) * (size_t)L, 256);
+    return align_up(sizeof(SelectState), 256) + align_up(sizeof(int64_t) * (size_t)(L + 1), 256);
 }
 
 int launch_select_salient(const float *salience, const int64_t *layer_offsets_host, int L, int64_t T, int32_t *selected,
                           int32_t *layer_counts, void *workspace, hipStream_t st)
 {
-    uint8_t *ws = (uint8_t *)workspace;
-    SelectState *state = (SelectState *)ws;
-    ws += align_up(sizeof(SelectState), 256);
-    int64_t *offsets = (int64_t *)ws;
-    ws += align_up(sizeof(int64_t) * (size_t)(L + 1), 256);
-    const size_t per = align_up(sizeof(uint32_t) * (size_t)L, 256);
-    uint32_t *gt = (uint32_t *)ws, *eq = (uint32_t *)(ws + per), *eq_take = (uint32_t *)(ws + 2 * per),
-             *out_off = (uint32_t *)(ws + 3 * per);
+    SelectState *state = (SelectState *)workspace;
+    int64_t *offsets = (int64_t *)((uint8_t *)workspace + align_up(sizeof(SelectState), 256));
     const int64_t total = layer_offsets_host[L];
+    hipLaunchKernelGGL(select_init_kernel, dim3((SEL_PASSES * SEL_BINS + 255) / 256), dim3(256), 0, st, state, (uint32_t)T, layer_counts, L);
+    if (T == 0) return (int)hipGetLastError();   // every list is empty
     for (int o = 0; o <= L; o += 128) {
         OffsetChunk c;
         const int n = std::min(128, L + 1 - o);
@@ -257,15 +315,19 @@ int launch_select_salient(const float *salience, const int64_t *layer_offsets_ho
         hipLaunchKernelGGL(select_offsets_kernel, dim3(1), dim3(128), 0, st, offsets + o, n, c);
     }
     const uint32_t *keys = (const uint32_t *)salience;
-    hipLaunchKernelGGL(select_init_kernel, dim3(1), dim3(256), 0, st, state, (uint32_t)T);
-    const int blocks = (int)std::min<int64_t>(2048, (total + 255) / 256);
-    for (int pass = 3; pass >= 0; --pass) {
-        if (blocks > 0) hipLaunchKernelGGL(select_hist_kernel, dim3(blocks), dim3(256), 0, st, keys, total, pass, state);
-        hipLaunchKernelGGL(select_pick_kernel, dim3(1), dim3(256), 0, st, state, pass);
-    }
-    hipLaunchKernelGGL(select_count_kernel, dim3(L), dim3(256), 0, st, keys, offsets, state, gt, eq);
-    hipLaunchKernelGGL(select_scan_kernel, dim3(1), dim3(64), 0, st, state, L, gt, eq, eq_take, out_off, layer_counts);
-    hipLaunchKernelGGL(select_emit_kernel, dim3(L), dim3(256), 0, st, keys, offsets, state, eq_take, out_off, selected);
+    const dim3 threads(SEL_THREADS);
+    // four keys a thread and at most one block per CU: more blocks are more atomics on one address, fewer
+    // leave the reads of a large model to too few CUs
+    const dim3 blocks((unsigned)std::min<int64_t>(256, (total + 4 * SEL_THREADS - 1) / (4 * SEL_THREADS)));
+    hipLaunchKernelGGL(select_hist_kernel<0>, blocks, threads, 0, st, keys, total, state);
+    hipLaunchKernelGGL(select_hist_kernel<1>, blocks, threads, 0, st, keys, total, state);
+    hipLaunchKernelGGL(select_hist_kernel<2>, blocks, threads, 0, st, keys, total, state);
+    // tiles of whole chunks of 1024 keys, at most SEL_MAX_TILES of them
+    const int64_t chunks = (total + SEL_THREADS - 1) / SEL_THREADS;
+    const int tile = (int)((chunks + SEL_MAX_TILES - 1) / SEL_MAX_TILES) * SEL_THREADS;
+    const dim3 tiles((unsigned)((total + tile - 1) / tile));
+    hipLaunchKernelGGL(select_count_kernel, tiles, threads, 0, st, keys, total, tile, state);
+    hipLaunchKernelGGL(select_emit_kernel, tiles, threads, 0, st, keys, total, tile, offsets, L, state, selected, layer_counts);
     return (int)hipGetLastError();
 }
 

@@ -729,6 +729,24 @@ def test_global_selection_matches_the_oracle_exactly(case):
     say(f"selection {case}: {len(layers)} layers, {total} channels")
 
 
+@pytest.mark.parametrize("case", ["empty_layers", "many_layers", "one_value", "several_chunks_per_tile", "one_channel"])
+def test_global_selection_at_tile_and_layer_edges(case):
+    rng = np.random.default_rng(23)
+    few = lambda n: rng.integers(0, 4, n).astype(np.float32)   # many channels share the threshold's value
+    layers = {
+        "empty_layers": [few(0), few(1023), few(0), few(0), few(1025), few(64), few(0)],
+        "many_layers": [few(int(n)) for n in rng.integers(0, 9, 1500)],          # more layers than offsets kept in LDS
+        "one_value": [np.full(n, 0.25, np.float32) for n in (1024, 2048, 5)],
+        "several_chunks_per_tile": [few(1 << 20), few(1025), few(3)],            # more than 1024 chunks of 1024 keys
+        "one_channel": [few(1)],
+    }[case]
+    total = sum(l.size for l in layers)
+    dl = [dev(l) for l in layers]
+    for T in sorted({0, 1, total // 3, total // 2 + 1, total}):
+        for a, b in zip(mx.select_salient(dl, T), ref.select_salient(layers, T), strict=True):
+            assert np.array_equal(a.cpu().numpy(), b), (case, T)
+
+
 def test_precision_search_end_to_end_feeds_the_linear():
     # Alg. 1 on three synthetic layers, then the chosen channels go into the weight quantizer and the
     # linear is checked against the oracle run with the same choice
