@@ -320,12 +320,8 @@ int mixllm_unpack_weights(const mixllm_desc *d, const void *packed_w8, const voi
     if (!buf_ok(packed_w8, s.w8_bytes) || !buf_ok(packed_w4, s.w4_bytes) || !buf_ok(scales8, s.scales8_bytes) ||
         !buf_ok(scales4, s.scales4_bytes) || !buf_ok(zeros4, s.zeros4_bytes))
         return MIXLLM_EINVAL;
-    hipStream_t st = (hipStream_t)stream;
-    if (perm != feature_perm &&
-        hipMemcpyAsync(perm, feature_perm, s.perm_bytes, hipMemcpyDeviceToDevice, st) != hipSuccess)
-        return MIXLLM_EHIP;
-    return hip_status(launch_unpack_weights(*d, packed_w8, packed_w4, scales8, scales4, zeros4, q8, s8, q4,
-                                            s4, z4, st));
+    return hip_status(launch_unpack_weights(*d, packed_w8, packed_w4, scales8, scales4, zeros4, feature_perm, q8, s8, q4,
+                                            s4, z4, perm == feature_perm ? nullptr : perm, (hipStream_t)stream));
 }
 
 int mixllm_quantize_activations(const mixllm_desc *d, const void *x, int8_t *xq, void *xscale, void *stream)

@@ -145,9 +145,10 @@ int launch_build_feature_perm(int N, int n8, const int32_t *salient_idx_dev, int
 int launch_pack_weights(const mixllm_desc &d, const int8_t *q8, const void *s8c, const uint8_t *q4,
                         const void *s4c, const uint8_t *z4c, void *w8, void *w4, void *s8,
                         void *s4, void *z4, hipStream_t st);
+// (perm: where the row order is copied to, or null)
 int launch_unpack_weights(const mixllm_desc &d, const void *w8, const void *w4, const void *s8,
-                          const void *s4, const void *z4, int8_t *q8, void *s8c, uint8_t *q4,
-                          void *s4c, uint8_t *z4c, hipStream_t st);
+                          const void *s4, const void *z4, const int32_t *feature_perm, int8_t *q8, void *s8c,
+                          uint8_t *q4, void *s4c, uint8_t *z4c, int32_t *perm, hipStream_t st);
 int launch_linear_generic(const LinearParams &p, hipStream_t st);
 int launch_linear_decode(const LinearParams &p, hipStream_t st);
 // evenly split decode variant

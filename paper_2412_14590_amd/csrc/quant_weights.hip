@@ -9,17 +9,6 @@ namespace mixllm {
 
 typedef half_t h8 __attribute__((ext_vector_type(8)));
 
-static __device__ inline float block_max_256(float v, float *red)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    v = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    __syncthreads();
-    return v;
-}
-
 // ------------------------------------------------- order of the concatenated rows --
 // feature_perm from a DEVICE list of the 8-bit channels (Sec. 3.4: the two parts own different
 // channel indices; Alg. 1's per-layer slice arrives on the device from mixllm_select_salient):
@@ -84,9 +73,66 @@ __global__ __launch_bounds__(1024) void perm_scan_kernel(int32_t *__restrict__ p
     for (int c = tid; c < N; c += 1024) perm[c] &= 0x7fffffff;
 }
 
+// The same for up to PERM_CHANNELS channels in one launch, with the marks as a bitmap in LDS: every block
+// builds the whole bitmap and the running count of marks per word for itself (the list is some
+// thousand entries) and places a share of the channels.  Three dependent launches, the last of them one
+// block walking 28 chunks of 1024 channels, took 16 us for 28672 channels,
+// this one 5.
+constexpr int PERM_CHANNELS = 1 << 17, PERM_SHARE = 4096;
+__global__ __launch_bounds__(1024) void perm_bitmap_kernel(const int32_t *__restrict__ idx, int n8, int32_t *__restrict__ perm, int N)
+{
+    __shared__ uint32_t bits[PERM_CHANNELS / 32];
+    __shared__ int before[PERM_CHANNELS / 32];   // marked channels in the words before
+    __shared__ int wave_tot[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int nwords = (N + 31) / 32, per = (nwords + 1023) / 1024, w0 = tid * per, w1 = min(w0 + per, nwords);
+    for (int w = tid; w < nwords; w += 1024) bits[w] = 0;
+    __syncthreads();
+    for (int i = tid; i < n8; i += 1024) {
+        const int c = idx[i];
+        if (c >= 0 && c < N) atomicOr(&bits[c >> 5], 1u << (c & 31));
+    }
+    __syncthreads();
+    int mine = 0;
+    for (int w = w0; w < w1; ++w) mine += __popc(bits[w]);
+    int inc = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += t;
+    }
+    if (lane == 63) wave_tot[wave] = inc;
+    __syncthreads();
+    int run = inc - mine, marked = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+        if (w < wave) run += wave_tot[w];
+        marked += wave_tot[w];
+    }
+    for (int w = w0; w < w1; ++w) {
+        before[w] = run;
+        run += __popc(bits[w]);
+    }
+    __syncthreads();
+    const int c_end = min(((int)blockIdx.x + 1) * PERM_SHARE, N);
+    for (int c = blockIdx.x * PERM_SHARE + tid; c < c_end; c += 1024) {
+        const uint32_t word = bits[c >> 5];
+        const int a = before[c >> 5] + __popc(word & ((1u << (c & 31)) - 1u));
+        const int pos = (word >> (c & 31)) & 1u ? a : n8 + (c - a);
+        if (pos < N) perm[pos] = c;
+    }
+    // (a list with fewer than n8 distinct valid channels leaves places free: still a channel number)
+    if (blockIdx.x == 0)
+        for (int i = marked + tid; i < n8; i += 1024) perm[i] = 0;
+}
+
 int launch_build_feature_perm(int N, int n8, const int32_t *salient_idx_dev, int32_t *perm, hipStream_t st)
 {
     if (N <= 0) return (int)hipSuccess;
+    if (N <= PERM_CHANNELS) {
+        hipLaunchKernelGGL(perm_bitmap_kernel, dim3((N + PERM_SHARE - 1) / PERM_SHARE), dim3(1024), 0, st, salient_idx_dev, n8, perm, N);
+        return (int)hipGetLastError();
+    }
     hipLaunchKernelGGL(perm_clear_kernel, dim3((N + 255) / 256), dim3(256), 0, st, perm, N);
     if (n8 > 0)
         hipLaunchKernelGGL(perm_mark_kernel, dim3((n8 + 255) / 256), dim3(256), 0, st, salient_idx_dev, n8, perm, N);
@@ -95,121 +141,168 @@ int launch_build_feature_perm(int N, int n8, const int32_t *salient_idx_dev, int
 }
 
 // ------------------------------------------------------------------ quantize + pack --
+// Bound by HBM: two bytes in, half a byte (or one) out per weight.  The lanes of a wave are the lanes
+// of the packed layout, lane = row of the tile + 16 * k-slot: a wave reads 16 rows x 256 bytes of one
+// group and writes the group's packed block as one contiguous KB.  (One block per row, the first
+// form, wrote 4-byte pieces 256 bytes apart, and the 16 rows that share a line ran on different
+// XCDs: 88 us for the 300 MB of K = 4096, N = 28672; this form 70, 4.3 TB/s.)
+// A unit of work is one tile of 16 rows x 8 groups, so that a row's metadata leaves as one 16-byte
+// (scales) and one 4-byte (zero points) store and the padding to a multiple of 8 groups falls out.
 
-// blocks [0, n8p): one 8-bit row each; blocks [n8p, n8p + n4p): one 4-bit row each.
-__global__ __launch_bounds__(256) void quantize_pack_kernel(
-    const half_t *__restrict__ W, const int32_t *__restrict__ perm, int K, int n8, int n4, int n8p,
+constexpr int QP_THREADS = 512, QP_WAVES = QP_THREADS / 64;
+
+// round(v / s) half to even for 16 values as the low bits of (round(v / s) + 1.5 * 2^23), the fp32
+// number whose mantissa holds the integer: the addition rounds exactly as rint does once the quotient
+// is clamped to whole limits, and replaces rint, a conversion and a mask.
+static __device__ inline uint32_t rounded_bits(half_t v, float s, float r, float lo, float hi)
+{
+    const float t = __builtin_amdgcn_fmed3f(quotient((float)v, s, r), lo, hi);
+    return __builtin_bit_cast(uint32_t, t + 12582912.0f);
+}
+constexpr uint32_t ROUND_BIAS = 0x4B400000u;   // bits of 1.5 * 2^23
+
+static __device__ inline void absmax16(const h8 &a, const h8 &b, float &amax)
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fmaxf(fabsf((float)a[i]), fabsf((float)b[i])));
+}
+static __device__ inline uint4 codes8x16(const h8 &a, const h8 &b, float s, float r)
+{
+    uint32_t w[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        uint32_t v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = rounded_bits(d < 2 ? a[4 * d + i] : b[4 * (d - 2) + i], s, r, -127.0f, 127.0f);
+        // the low byte of each
+        w[d] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(v[3], v[2], 0x0c0c0400u), __builtin_amdgcn_perm(v[1], v[0], 0x0c0c0400u), 0x05040100u);
+    }
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// blocks [0, n8p / 16): one tile of 16 8-bit rows each; the others: QP_WAVES units of the 4-bit part each
+__global__ __launch_bounds__(QP_THREADS) void quantize_pack_kernel(
+    const half_t *__restrict__ W, const int32_t *__restrict__ perm, int K, int n8, int n4, int n8p, int n4p,
     int ng, int ngp, int w8_per_channel, int8_t *__restrict__ w8, uint8_t *__restrict__ w4,
     half_t *__restrict__ s8, half_t *__restrict__ s4, uint8_t *__restrict__ z4)
 {
-    __shared__ float red[4];
-    const int tid = threadIdx.x;
-    const int nsteps = K / 64;
-    if ((int)blockIdx.x < n8p) {
-        // ---- 8-bit row: thread handles 16 consecutive k (one packed slot) per iteration
-        const int r = blockIdx.x;
-        const bool real = r < n8;
-        const half_t *row = real ? W + (size_t)perm[r] * K : nullptr;
-        const int nchunk = K / 16;
-        float s_row = 1.0f;
+    __shared__ float row_scale[TILE_N];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int r16 = lane & 15, ks = lane >> 4;
+    const h8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+    if ((int)blockIdx.x < n8p / TILE_N) {
+        // ---- a tile of 8-bit rows: (one scale per channel: each wave finds the maxima of two rows, the
+        //      second read of the tile comes from the L2), then every wave takes every QP_WAVES-th group
+        const int r0 = blockIdx.x * TILE_N;
         if (w8_per_channel) {
-            float amax = 0.0f;
-            if (real)
-                for (int c = tid; c < nchunk; c += 256) {
-                    h8 a = *(const h8 *)(row + c * 16), b = *(const h8 *)(row + c * 16 + 8);
-#pragma unroll
-                    for (int i = 0; i < 8; ++i)
-                        amax = fmaxf(amax, fmaxf(fabsf((float)a[i]), fabsf((float)b[i])));
+            for (int i = wave; i < TILE_N; i += QP_WAVES) {
+                const bool real = r0 + i < n8;
+                float amax = 0.0f;
+                if (real) {
+                    const half_t *row = W + (size_t)perm[r0 + i] * K;
+                    for (int k = lane * 16; k < K; k += 1024) absmax16(*(const h8 *)(row + k), *(const h8 *)(row + k + 8), amax);
                 }
-            amax = block_max_256(amax, red);
-            half_t s16 = real ? store_scale(amax / 127.0f) : (half_t)0.0f;
-            if (tid == 0) s8[r] = s16;
-            s_row = (float)s16;
-        } else {
-            // zero the metadata padding of this row (groups ng..ngp-1)
-            for (int g = ng + tid; g < ngp; g += 256) s8[(size_t)r * ngp + g] = (half_t)0.0f;
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+                if (lane == 0) {
+                    const half_t s16 = real ? store_scale(amax / 127.0f) : (half_t)0.0f;
+                    s8[r0 + i] = s16;
+                    row_scale[i] = (float)s16;
+                }
+            }
+            __syncthreads();
         }
-        // nchunk is a multiple of 8, so the 8 lanes of one group are always active together
-        for (int c = tid; c < nchunk; c += 256) {
-            uint4 out = make_uint4(0, 0, 0, 0);
-            float s = s_row;
+        const int r = r0 + r16;
+        const bool real = r < n8;
+        const half_t *row = W + (size_t)(real ? perm[r] : 0) * K;
+        float s = w8_per_channel ? row_scale[r16] : 0.0f, rs = recip(s);
+        uint4 *out = (uint4 *)w8 + (size_t)blockIdx.x * (K / 64) * 64 + lane;
+        for (int g = wave; g < (w8_per_channel ? ng : ngp); g += QP_WAVES) {
+            if (g >= ng) {   // padding of the per-group scales
+                if (ks == 0) s8[(size_t)r * ngp + g] = (half_t)0.0f;
+                continue;
+            }
+            const half_t *src = row + g * G + ks * 16;   // 16 values in each half of the group
+            h8 v[4] = {zero8, zero8, zero8, zero8};
             if (real) {
-                h8 a = *(const h8 *)(row + c * 16), b = *(const h8 *)(row + c * 16 + 8);
-                if (!w8_per_channel) {
-                    float amax = 0.0f;
-#pragma unroll
-                    for (int i = 0; i < 8; ++i)
-                        amax = fmaxf(amax, fmaxf(fabsf((float)a[i]), fabsf((float)b[i])));
-#pragma unroll
-                    for (int o = 4; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 8));
-                    half_t s16 = store_scale(amax / 127.0f);
-                    if ((c & 7) == 0) s8[(size_t)r * ngp + (c >> 3)] = s16;
-                    s = (float)s16;
-                }
-                uint32_t w[4] = {0, 0, 0, 0};
-                const float rs = recip(s);
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    float v = (i < 8) ? (float)a[i] : (float)b[i - 8];
-                    float t = fminf(fmaxf(__builtin_rintf(quotient(v, s, rs)), -127.0f), 127.0f);
-                    w[i >> 2] |= ((uint32_t)(int)t & 0xffu) << (8 * (i & 3));
-                }
-                out = make_uint4(w[0], w[1], w[2], w[3]);
-            } else if (!w8_per_channel && (c & 7) == 0) {
-                s8[(size_t)r * ngp + (c >> 3)] = (half_t)0.0f;
+                v[0] = *(const h8 *)src;
+                v[1] = *(const h8 *)(src + 8);
+                v[2] = *(const h8 *)(src + 64);
+                v[3] = *(const h8 *)(src + 72);
             }
-            *(uint4 *)((uint8_t *)w8 + w8_slot_offset(r, c >> 2, c & 3, nsteps)) = out;
+            if (!w8_per_channel) {
+                float amax = 0.0f;
+                absmax16(v[0], v[1], amax);
+                absmax16(v[2], v[3], amax);
+                amax = fmaxf(amax, __shfl_xor(amax, 16, 64));
+                amax = fmaxf(amax, __shfl_xor(amax, 32, 64));
+                const half_t s16 = real ? store_scale(amax / 127.0f) : (half_t)0.0f;
+                if (ks == 0) s8[(size_t)r * ngp + g] = s16;
+                s = (float)s16;
+                rs = recip(s);
+            }
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf)
+                out[(size_t)(2 * g + hf) * 64] = real ? codes8x16(v[2 * hf], v[2 * hf + 1], s, rs) : make_uint4(0, 0, 0, 0);
         }
-    } else {
-        // ---- 4-bit row: 16 lanes per group, 8 consecutive k (one packed dword) per lane
-        const int r = blockIdx.x - n8p;
-        const bool real = r < n4;
-        const half_t *row = real ? W + (size_t)perm[n8 + r] * K : nullptr;
-        const int sub = tid >> 4, i16 = tid & 15;
-        for (int g0 = 0; g0 < ngp; g0 += 16) {
-            const int g = g0 + sub;
-            float sc = 0.0f, zf = 0.0f;
-            half_t s16 = (half_t)0.0f;
-            uint32_t packed = 0;
-            if (real && g < ng) {
-                h8 v = *(const h8 *)(row + (size_t)g * G + i16 * 8);
-                float mn = 0.0f, mx = 0.0f;   // the range always contains 0
+        return;
+    }
+    // ---- a unit of the 4-bit part
+    const int upt = ngp / 8;   // units per tile
+    const int unit = ((int)blockIdx.x - n8p / TILE_N) * QP_WAVES + wave;
+    if (unit >= n4p / TILE_N * upt) return;
+    const int tile = unit / upt, g0 = (unit - tile * upt) * 8;
+    const int r = tile * TILE_N + r16;
+    const bool real = r < n4;
+    const half_t *row = W + (size_t)(real ? perm[n8 + r] : 0) * K + ks * 16;
+    uint4 *out = (uint4 *)w4 + ((size_t)tile * ng + g0) * 64 + lane;
+    uint32_t scales[4] = {0, 0, 0, 0}, zeros = 0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        if (g0 + u >= ng) break;   // (the metadata of these padding groups is zero)
+        uint4 packed = make_uint4(0, 0, 0, 0);
+        half_t s16 = (half_t)0.0f;
+        int z = 0;
+        if (real) {
+            const half_t *src = row + (g0 + u) * G;
+            const h8 v[4] = {*(const h8 *)src, *(const h8 *)(src + 8), *(const h8 *)(src + 64), *(const h8 *)(src + 72)};
+            float mn = 0.0f, mx = 0.0f;   // the range always contains 0
+#pragma unroll
+            for (int d = 0; d < 4; ++d)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    mn = fminf(mn, (float)v[i]);
-                    mx = fmaxf(mx, (float)v[i]);
+                    mn = fminf(mn, (float)v[d][i]);
+                    mx = fmaxf(mx, (float)v[d][i]);
                 }
 #pragma unroll
-                for (int o = 8; o > 0; o >>= 1) {
-                    mn = fminf(mn, __shfl_xor(mn, o, 16));
-                    mx = fmaxf(mx, __shfl_xor(mx, o, 16));
-                }
-                s16 = store_scale((mx - mn) / 15.0f);
-                sc = (float)s16;
-                const float rsc = recip(sc);
-                zf = fminf(fmaxf(__builtin_rintf(quotient(-mn, sc, rsc)), 0.0f), 15.0f);
-                uint32_t code[8];
+            for (int o = 16; o < 64; o <<= 1) {
+                mn = fminf(mn, __shfl_xor(mn, o, 64));
+                mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+            }
+            s16 = store_scale((mx - mn) / 15.0f);
+            const float sc = (float)s16, rsc = recip(sc);
+            const float zf = fminf(fmaxf(__builtin_rintf(quotient(-mn, sc, rsc)), 0.0f), 15.0f);
+            z = (int)zf;
+            // code = clamp(round(v / s) + z, 0, 15), the limits moved to the other side of the sum; the
+            // eight biases of a dword are taken off (and z added) in one addition modulo 2^32
+            const uint32_t fix = ((uint32_t)z - ROUND_BIAS) * 0x11111111u;
+            uint32_t w[4];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    float t = __builtin_rintf(quotient((float)v[i], sc, rsc)) + zf;
-                    code[i] = (uint32_t)(int)fminf(fmaxf(t, 0.0f), 15.0f);
-                }
+            for (int d = 0; d < 4; ++d) {
+                w[d] = fix;
 #pragma unroll
-                for (int b = 0; b < 4; ++b) packed |= (code[b] | (code[b + 4] << 4)) << (8 * b);
+                for (int i = 0; i < 8; ++i)   // byte b of a dword: k-local b in the low nibble, b + 4 in the high one
+                    w[d] += rounded_bits(v[d][i], sc, rsc, -zf, 15.0f - zf) << (8 * (i & 3) + (i & 4));
             }
-            if (g < ng) {
-                // lane i16 holds k-local 8*i16..+7: 16-k chunk c = i16/2, dword i16%2
-                const int c = i16 >> 1, ks = c & 3, half = c >> 2;
-                *(uint32_t *)(w4 + w4_slot_offset(r, g, ks, ng) + half * 8 + (i16 & 1) * 4) = packed;
-            }
-            // metadata, including the zero padding up to ngp
-            int z = (int)zf;
-            int z_next = __shfl_down(z, 16, 64);   // zero point of group g+1 (next 16-lane set)
-            if (i16 == 0 && g < ngp) {
-                s4[(size_t)r * ngp + g] = s16;
-                if ((sub & 1) == 0) z4[(size_t)r * (ngp / 2) + (g >> 1)] = (uint8_t)(z | (z_next << 4));
-            }
+            packed = make_uint4(w[0], w[1], w[2], w[3]);
         }
+        out[u * 64] = packed;
+        scales[u >> 1] |= (uint32_t)__builtin_bit_cast(uint16_t, s16) << (16 * (u & 1));
+        zeros |= (uint32_t)z << (4 * u);
+    }
+    if (ks == 0) {
+        *(uint4 *)(s4 + (size_t)r * ngp + g0) = make_uint4(scales[0], scales[1], scales[2], scales[3]);
+        *(uint32_t *)(z4 + (size_t)r * (ngp / 2) + g0 / 2) = zeros;
     }
 }
 
@@ -219,8 +312,9 @@ int launch_quantize_weights(const mixllm_desc &d, const void *W, void *w8, void 
     const int n4 = d.N - d.n8, n8p = round_up(d.n8, TILE_N), n4p = round_up(n4, TILE_N);
     const int ng = d.K / G, ngp = round_up(ng, 8);
     if (n8p + n4p == 0) return hipSuccess;
-    hipLaunchKernelGGL(quantize_pack_kernel, dim3(n8p + n4p), dim3(256), 0, st, (const half_t *)W,
-                       perm, d.K, d.n8, n4, n8p, ng, ngp, d.w8_group == d.K ? 1 : 0, (int8_t *)w8,
+    const int units = n4p / TILE_N * (ngp / 8);
+    hipLaunchKernelGGL(quantize_pack_kernel, dim3(n8p / TILE_N + (units + QP_WAVES - 1) / QP_WAVES), dim3(QP_THREADS), 0, st,
+                       (const half_t *)W, perm, d.K, d.n8, n4, n8p, n4p, ng, ngp, d.w8_group == d.K ? 1 : 0, (int8_t *)w8,
                        (uint8_t *)w4, (half_t *)s8, (half_t *)s4, (uint8_t *)z4);
     return (int)hipGetLastError();
 }
@@ -323,80 +417,87 @@ int launch_pack_weights(const mixllm_desc &d, const int8_t *q8, const void *s8c,
 }
 
 // ------------------------------------------------------------ packed -> canonical --
+// Bound by HBM (half a byte or one in, one out per weight).  Lanes and units are those of
+// quantize_pack_kernel: a wave reads packed blocks as they lie, 1 KB at a time, and writes 16 bytes per
+// lane, both halves of every 128-byte piece of a row.  One launch for codes, scales, zero points and the
+// row order of both parts.  (A thread per packed dword with byte stores took 50 us for the 4-bit part of
+// K = 4096, N = 28672, 158 MB, and the five launches beside it 35; this launch 39, 4.8 TB/s.)
 
-__global__ __launch_bounds__(256) void unpack_w4_kernel(const uint32_t *__restrict__ w4, int n4, int K,
-                                                        int ng, uint8_t *__restrict__ q4)
+template <bool ALIGNED>   // of the 4-bit codes, the one array of codes that may start at any byte
+__global__ __launch_bounds__(256) void unpack_kernel(const uint4 *__restrict__ w8, const uint4 *__restrict__ w4,
+                                                     const half_t *__restrict__ s8, const half_t *__restrict__ s4,
+                                                     const uint8_t *__restrict__ z4, const int32_t *__restrict__ feature_perm, int K, int N,
+                                                     int n8, int n4, int ng, int ngp, int w8_per_channel, int units8, int units4,
+                                                     int8_t *__restrict__ q8, half_t *__restrict__ s8c, uint8_t *__restrict__ q4,
+                                                     half_t *__restrict__ s4c, uint8_t *__restrict__ z4c, int32_t *__restrict__ perm)
 {
-    const size_t total = (size_t)n4 * K / 8;   // one packed dword (8 codes) per thread
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
-        const int r = (int)(i / (K / 8));
-        const int k0 = (int)(i % (K / 8)) * 8;           // canonical k of the first code
-        const int g = k0 / G, kl = k0 % G;
-        const int half = kl / 64, ks = (kl % 64) / 16, d = (kl % 16) / 8;
-        const uint32_t w = *(const uint32_t *)((const uint8_t *)w4 + w4_slot_offset(r, g, ks, ng) +
-                                               half * 8 + d * 4);
-        uint8_t *dst = q4 + (size_t)r * K + k0;
+    const int lane = threadIdx.x & 63, r16 = lane & 15, ks = lane >> 4, upt = ngp / 8;
+    int unit = (int)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (unit < units8) {
+        const int tile = unit / upt, g0 = (unit - tile * upt) * 8, r = tile * TILE_N + r16;
+        if (r >= n8) return;
+        const uint4 *src = w8 + ((size_t)tile * ng + g0) * 128 + lane;
+        int8_t *dst = q8 + (size_t)r * K + g0 * G + ks * 16;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            dst[b] = (uint8_t)((w >> (8 * b)) & 15);
-            dst[b + 4] = (uint8_t)((w >> (8 * b + 4)) & 15);
+        for (int u = 0; u < 8; ++u)
+            if (g0 + u < ng) {
+                *(uint4 *)(dst + u * G) = src[u * 128];
+                *(uint4 *)(dst + u * G + 64) = src[u * 128 + 64];
+            }
+        if (w8_per_channel) {
+            if (g0 == 0 && ks == 0) s8c[r] = s8[r];
+        } else
+            for (int g = g0 + 2 * ks; g < min(g0 + 2 * ks + 2, ng); ++g) s8c[(size_t)r * ng + g] = s8[(size_t)r * ngp + g];
+        return;
+    }
+    unit -= units8;
+    if (unit < units4) {
+        const int tile = unit / upt, g0 = (unit - tile * upt) * 8, r = tile * TILE_N + r16;
+        if (r >= n4) return;
+        const uint4 *src = w4 + ((size_t)tile * ng + g0) * 64 + lane;
+        uint8_t *dst = q4 + (size_t)r * K + g0 * G + ks * 16;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (g0 + u < ng) {
+                const uint4 v = src[u * 64];
+                const uint32_t lo = 0x0F0F0F0Fu;
+                const uint4 c[2] = {make_uint4(v.x & lo, (v.x >> 4) & lo, v.y & lo, (v.y >> 4) & lo),
+                                    make_uint4(v.z & lo, (v.z >> 4) & lo, v.w & lo, (v.w >> 4) & lo)};
+#pragma unroll
+                for (int hf = 0; hf < 2; ++hf) {
+                    uint8_t *o = dst + u * G + hf * 64;
+                    if (ALIGNED) *(uint4 *)o = c[hf];
+                    else {
+                        const uint32_t d[4] = {c[hf].x, c[hf].y, c[hf].z, c[hf].w};
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) o[i] = (uint8_t)(d[i >> 2] >> (8 * (i & 3)));
+                    }
+                }
+            }
+        for (int g = g0 + 2 * ks; g < min(g0 + 2 * ks + 2, ng); ++g) {
+            s4c[(size_t)r * ng + g] = s4[(size_t)r * ngp + g];
+            z4c[(size_t)r * ng + g] = (uint8_t)z4_load(z4, r, g, ngp);
         }
+        return;
     }
+    const int j = (unit - units4) * 64 + lane;
+    if (perm && j < N) perm[j] = feature_perm[j];
 }
 
-__global__ __launch_bounds__(256) void unpack_w8_kernel(const uint4 *__restrict__ w8, int n8, int K,
-                                                        int8_t *__restrict__ q8)
+int launch_unpack_weights(const mixllm_desc &d, const void *w8, const void *w4, const void *s8, const void *s4, const void *z4,
+                          const int32_t *feature_perm, int8_t *q8, void *s8c, uint8_t *q4, void *s4c, uint8_t *z4c, int32_t *perm,
+                          hipStream_t st)
 {
-    const int nsteps = K / 64;
-    const size_t total = (size_t)n8 * K / 16;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
-        const int r = (int)(i / (K / 16)), c = (int)(i % (K / 16));
-        *(uint4 *)(q8 + (size_t)r * K + c * 16) =
-            *(const uint4 *)((const uint8_t *)w8 + w8_slot_offset(r, c >> 2, c & 3, nsteps));
-    }
-}
-
-__global__ __launch_bounds__(256) void unpack_scales_kernel(const half_t *__restrict__ src, int rows,
-                                                            int ncan, int nstride,
-                                                            half_t *__restrict__ dst)
-{
-    const size_t total = (size_t)rows * ncan;
-    for (size_t o = (size_t)blockIdx.x * 256 + threadIdx.x; o < total; o += (size_t)gridDim.x * 256)
-        dst[o] = src[(o / ncan) * nstride + (o % ncan)];
-}
-
-__global__ __launch_bounds__(256) void unpack_zeros_kernel(const uint8_t *__restrict__ z4, int n4, int ng,
-                                                           int ngp, uint8_t *__restrict__ z4c)
-{
-    const size_t total = (size_t)n4 * ng;
-    for (size_t o = (size_t)blockIdx.x * 256 + threadIdx.x; o < total; o += (size_t)gridDim.x * 256) {
-        const int r = (int)(o / ng), g = (int)(o % ng);
-        const uint8_t b = z4[(size_t)r * (ngp / 2) + (g >> 1)];
-        z4c[o] = (g & 1) ? (b >> 4) : (b & 15);
-    }
-}
-
-int launch_unpack_weights(const mixllm_desc &d, const void *w8, const void *w4, const void *s8,
-                          const void *s4, const void *z4, int8_t *q8, void *s8c, uint8_t *q4,
-                          void *s4c, uint8_t *z4c, hipStream_t st)
-{
-    const int n4 = d.N - d.n8;
-    const int ng = d.K / G, ngp = round_up(ng, 8);
-    if (n4) {
-        hipLaunchKernelGGL(unpack_w4_kernel, dim3(grid_for((size_t)n4 * d.K / 8)), dim3(256), 0, st,
-                           (const uint32_t *)w4, n4, d.K, ng, q4);
-        hipLaunchKernelGGL(unpack_scales_kernel, dim3(grid_for((size_t)n4 * ng)), dim3(256), 0, st,
-                           (const half_t *)s4, n4, ng, ngp, (half_t *)s4c);
-        hipLaunchKernelGGL(unpack_zeros_kernel, dim3(grid_for((size_t)n4 * ng)), dim3(256), 0, st,
-                           (const uint8_t *)z4, n4, ng, ngp, z4c);
-    }
-    if (d.n8) {
-        hipLaunchKernelGGL(unpack_w8_kernel, dim3(grid_for((size_t)d.n8 * d.K / 16)), dim3(256), 0, st,
-                           (const uint4 *)w8, d.n8, d.K, q8);
-        const int ncan = d.w8_group == d.K ? 1 : ng, nstride = d.w8_group == d.K ? 1 : ngp;
-        hipLaunchKernelGGL(unpack_scales_kernel, dim3(grid_for((size_t)d.n8 * ncan)), dim3(256), 0, st,
-                           (const half_t *)s8, d.n8, ncan, nstride, (half_t *)s8c);
-    }
+    const int n4 = d.N - d.n8, ng = d.K / G, ngp = round_up(ng, 8), upt = ngp / 8;
+    const int units8 = round_up(d.n8, TILE_N) / TILE_N * upt, units4 = round_up(n4, TILE_N) / TILE_N * upt;
+    const int units = units8 + units4 + (perm ? (d.N + 63) / 64 : 0);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((units + 3) / 4), dim3(256), 0, st, (const uint4 *)w8, (const uint4 *)w4, (const half_t *)s8,
+                           (const half_t *)s4, (const uint8_t *)z4, feature_perm, d.K, d.N, d.n8, n4, ng, ngp, d.w8_group == d.K ? 1 : 0,
+                           units8, units4, q8, (half_t *)s8c, q4, (half_t *)s4c, z4c, perm);
+    };
+    if (((uintptr_t)q4 & 15u) == 0) go(unpack_kernel<true>);
+    else go(unpack_kernel<false>);
     return (int)hipGetLastError();
 }
 

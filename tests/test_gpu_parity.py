@@ -160,6 +160,31 @@ def test_feature_perm_is_built_on_the_device_from_a_device_list(N, n8):
     assert np.array_equal(PL.perm.cpu().numpy(), ref.feature_perm(N, sal))
 
 
+@pytest.mark.parametrize("K,N,n8", [(128, 4097, 4096), (128, 131072, 1000), (128, 131073, 131), (1152, 15, 1), (2048, 65, 33)])
+@pytest.mark.parametrize("w8_group", [None, 128])
+def test_conversion_at_the_edges_of_tiles_and_units(K, N, n8, w8_group):
+    # row orders on both sides of the bitmap's limit and of a block's share; rows and groups that do not
+    # fill a tile of 16 or a unit of 8 groups; the 4-bit codes exported to an address that is not aligned
+    rng = np.random.default_rng(N)
+    W = (rng.standard_normal((N, K)) * 0.02).astype(np.float16)
+    sal = rng.permutation(N)[:n8].astype(np.int32)
+    L = ref.quantize_weights(W, sal, G, w8_group)
+    P = mx.quantize_weights(dev(W), dev(sal), w8_group)
+    u = mx.unpack_weights(P)
+    for k in ("q8", "q4", "z4", "perm"):
+        assert np.array_equal(u[k].cpu().numpy(), getattr(L, k)), k
+    for k in ("s8", "s4"):
+        assert np.array_equal(u[k].cpu().numpy().view(np.uint16), getattr(L, k).view(np.uint16)), k
+    import ctypes as C
+    q4 = torch.full(((N - n8) * K + 32,), 99, dtype=torch.uint8, device="cuda")
+    d = P.desc()
+    rc = mx.lib().mixllm_unpack_weights(C.byref(d), *[t.data_ptr() for t in (P.w8, P.w4, P.s8, P.s4, P.z4, P.perm, u["q8"], u["s8"])],
+                                        q4.data_ptr() + 3, *[u[k].data_ptr() for k in ("s4", "z4", "perm")], None)
+    assert rc == 0
+    torch.cuda.synchronize()
+    assert torch.equal(q4[3:-29].view(N - n8, K), u["q4"]) and bool((q4[:3] == 99).all()) and bool((q4[-29:] == 99).all())
+
+
 def test_a_bad_device_list_of_8bit_channels_never_writes_out_of_bounds():
     # indices out of range are ignored, duplicates count once; the order is then unspecified, but
     # every entry stays a channel number and the buffers around feature_perm are untouched
