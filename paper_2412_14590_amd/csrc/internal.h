@@ -119,14 +119,32 @@ static inline __device__ float quotient(float v, float s, float r)
     const float e = __builtin_fmaf(-t0, s, v);
     return __builtin_fmaf(e, r, t0);
 }
-// one int8 code: v / s rounded half to even, clamped to [-127, 127]; returned in the low byte
-static inline __device__ uint32_t quant_code(half_t v, float s, float r)
+// v / s clamped to whole limits and rounded half to even, as the low bits of the sum with 1.5 * 2^23:
+// that fp32 number's mantissa holds the integer in two's complement, the addition rounds exactly as rint
+// does (and clamping first gives what clamping the rounded value gives), and one instruction takes the
+// place of rint, a conversion to integer and a mask.
+constexpr uint32_t ROUND_BIAS = 0x4B400000u;   // bits of 1.5 * 2^23
+static inline __device__ uint32_t rounded_bits(half_t v, float s, float r, float lo, float hi)
 {
-    float t = __builtin_rintf(quotient((float)v, s, r));
-    t = fminf(fmaxf(t, -127.0f), 127.0f);
-    return (uint32_t)(int)t & 0xffu;
+    const float t = __builtin_amdgcn_fmed3f(quotient((float)v, s, r), lo, hi);
+    return __builtin_bit_cast(uint32_t, t + 12582912.0f);
 }
-// the same with the IEEE division (the reference of the exhaustive check)
+// one int8 code in the low byte (the bytes above it are not zero)
+static inline __device__ uint32_t quant_bits(half_t v, float s, float r) { return rounded_bits(v, s, r, -127.0f, 127.0f); }
+static inline __device__ uint32_t pack_low_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
+{
+    return __builtin_amdgcn_perm(__builtin_amdgcn_perm(d, c, 0x0c0c0400u), __builtin_amdgcn_perm(b, a, 0x0c0c0400u), 0x05040100u);
+}
+// codes of 8 values, value i in byte i
+typedef half_t h8 __attribute__((ext_vector_type(8)));
+static inline __device__ uint2 quant8(const h8 &v, float s, float r)
+{
+    uint32_t b[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) b[i] = quant_bits(v[i], s, r);
+    return make_uint2(pack_low_bytes(b[0], b[1], b[2], b[3]), pack_low_bytes(b[4], b[5], b[6], b[7]));
+}
+// one int8 code with the IEEE division (the reference of the exhaustive check)
 static inline __device__ uint32_t quant_code_ieee(half_t v, float s)
 {
     float t = __builtin_rintf((float)v / s);

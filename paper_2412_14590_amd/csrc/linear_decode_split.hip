@@ -58,7 +58,6 @@ constexpr size_t LDS_LIMIT = 156 * 1024;
 #define MIXLLM_SPLIT_EARLY 1   // how many of them go out together with the activation loads
 #endif
 
-typedef half_t h8 __attribute__((ext_vector_type(8)));
 
 struct SplitArgs {
     int nblk8, nblk4;   // blocks of the 8-bit and of the 4-bit part
@@ -335,15 +334,10 @@ __device__ inline void split_block(const LinearParams &p, const SplitArgs &a, ui
                 for (int o = 8; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
                 const float sc = (float)store_scale(amax / 127.0f);
                 const float rc = recip(sc);
-                uint32_t w0 = 0, w1 = 0;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    w0 |= quant_code(hv[e], sc, rc) << (8 * e);
-                    w1 |= quant_code(hv[4 + e], sc, rc) << (8 * e);
-                }
+                const uint2 codes = quant8(hv, sc, rc);
                 if (i < npiece) {
                     const int tok = i / per_row, pos = i - tok * per_row;
-                    *(uint2 *)(lds_x + tok * xstride + pos * 8) = make_uint2(w0, w1);
+                    *(uint2 *)(lds_x + tok * xstride + pos * 8) = codes;
                     if ((lane & 15) == 0) xsg[tok * ng + (pos >> 4)] = sc;
                 }
             }
@@ -375,13 +369,8 @@ __device__ inline void split_block(const LinearParams &p, const SplitArgs &a, ui
                 const float sc = (float)store_scale(__builtin_bit_cast(float, tokmax[tok]) / 127.0f);
                 const float rc = recip(sc);
                 const h8 hv = __builtin_bit_cast(h8, xv[j]);
-                uint32_t w0 = 0, w1 = 0;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    w0 |= quant_code(hv[e], sc, rc) << (8 * e);
-                    w1 |= quant_code(hv[4 + e], sc, rc) << (8 * e);
-                }
-                *(uint2 *)(lds_x + tok * xstride + pos * 8) = make_uint2(w0, w1);
+                const uint2 codes = quant8(hv, sc, rc);
+                *(uint2 *)(lds_x + tok * xstride + pos * 8) = codes;
             }
         }
 #pragma unroll
@@ -414,13 +403,8 @@ __device__ inline void split_block(const LinearParams &p, const SplitArgs &a, ui
             const int i = tid + NT * j;
             if (j * NT < npiece && i < npiece) {
                 const h8 hv = __builtin_bit_cast(h8, xv[j]);   // the whole register, after its wait
-                uint32_t w0 = 0, w1 = 0;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    w0 |= quant_code(hv[e], sc, rc) << (8 * e);
-                    w1 |= quant_code(hv[4 + e], sc, rc) << (8 * e);
-                }
-                *(uint2 *)(lds_x + i * 8) = make_uint2(w0, w1);
+                const uint2 codes = quant8(hv, sc, rc);
+                *(uint2 *)(lds_x + i * 8) = codes;
             }
         }
 #pragma unroll

@@ -5,8 +5,6 @@
 
 namespace mixllm {
 
-typedef half_t h8 __attribute__((ext_vector_type(8)));
-
 static __device__ inline float wave_max(float v)
 {
 #pragma unroll
@@ -14,15 +12,20 @@ static __device__ inline float wave_max(float v)
     return v;
 }
 
-static __device__ inline uint2 quant8(const h8 &v, float s)
+// largest magnitude of 8 values, folded into a pair of running maxima: fp16 magnitudes order like
+// their bit patterns, so the maximum is a packed one of 16-bit integers (one instruction per value
+// with the mask; a conversion and an fp32 maximum each took two)
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+static __device__ inline void absmax8(const h8 &v, u16x2 &m)
 {
-    const float r = recip(s);
-    uint32_t w[2] = {0u, 0u};
+    const uint4 w = __builtin_bit_cast(uint4, v);
+    const uint32_t d[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        w[i >> 2] |= quant_code(v[i], s, r) << (8 * (i & 3));
-    }
-    return make_uint2(w[0], w[1]);
+    for (int i = 0; i < 4; ++i) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, d[i] & 0x7fff7fffu));
+}
+static __device__ inline float absmax_of(u16x2 m)
+{
+    return (float)__builtin_bit_cast(half_t, (uint16_t)max(m.x, m.y));
 }
 
 // Exhaustive check of quotient(): for every positive finite fp16 scale (one block each) and every
@@ -36,7 +39,7 @@ __global__ __launch_bounds__(256) void check_fast_division_kernel(unsigned long 
     for (int xb = threadIdx.x; xb < 65536; xb += 256) {
         if ((xb & 0x7C00) == 0x7C00) continue;   // infinities and NaNs
         const half_t x = __builtin_bit_cast(half_t, (uint16_t)xb);
-        bad += quant_code(x, s, r) != quant_code_ieee(x, s);
+        bad += (quant_bits(x, s, r) & 0xffu) != quant_code_ieee(x, s);
         // the 4-bit weight quantizer rounds the same quotient without the int8 clamp
         bad += __builtin_rintf(quotient((float)x, s, r)) != __builtin_rintf((float)x / s);
     }
@@ -44,67 +47,64 @@ __global__ __launch_bounds__(256) void check_fast_division_kernel(unsigned long 
 }
 
 // One block per token, the row held in registers between the absmax pass and the quantizing
-// pass (up to NV vectors of 8 per thread: K <= 2048 * NV): one trip to memory instead of two,
+// pass (NV vectors of 8 per thread: K <= 8 * NV * THREADS): one trip to memory instead of two,
 // which is most of the duration of this kernel when M is small.
-template <int NV>
-__global__ __launch_bounds__(256) void act_quant_per_token_regs(const half_t *__restrict__ x,
-                                                                int8_t *__restrict__ xq,
-                                                                half_t *__restrict__ xs, int K)
+template <int NV, int THREADS>
+__global__ __launch_bounds__(THREADS) void act_quant_per_token_regs(const half_t *__restrict__ x,
+                                                                    int8_t *__restrict__ xq,
+                                                                    half_t *__restrict__ xs, int K)
 {
-    __shared__ float red[4];
+    __shared__ float red[THREADS / 64];
     const int m = blockIdx.x;
     const h8 *row = (const h8 *)(x + (size_t)m * K);
     const int nvec = K / 8;
     h8 d[NV];
-    float amax = 0.0f;
+    u16x2 am = {0, 0};
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
-        const int v = threadIdx.x + 256 * j;
-        if (v < nvec) {
-            d[j] = row[v];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf((float)d[j][i]));
-        }
+        const int v = threadIdx.x + THREADS * j;
+        if (v < nvec) d[j] = row[v];
     }
-    amax = wave_max(amax);
+#pragma unroll
+    for (int j = 0; j < NV; ++j)
+        if ((int)threadIdx.x + THREADS * j < nvec) absmax8(d[j], am);
+    float amax = wave_max(absmax_of(am));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = amax;
     __syncthreads();
-    amax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+#pragma unroll
+    for (int w = 0; w < THREADS / 64; ++w) amax = fmaxf(amax, red[w]);
     half_t s16 = store_scale(amax / 127.0f);
-    float s = (float)s16;
+    const float s = (float)s16, r = recip(s);
     if (threadIdx.x == 0) xs[m] = s16;
     uint2 *out = (uint2 *)(xq + (size_t)m * K);
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
-        const int v = threadIdx.x + 256 * j;
-        if (v < nvec) out[v] = quant8(d[j], s);
+        const int v = threadIdx.x + THREADS * j;
+        if (v < nvec) out[v] = quant8(d[j], s, r);
     }
 }
 
 // One block per token, any K; the row is read twice (the second read hits L2).
-__global__ __launch_bounds__(256) void act_quant_per_token(const half_t *__restrict__ x,
-                                                           int8_t *__restrict__ xq,
-                                                           half_t *__restrict__ xs, int K)
+__global__ __launch_bounds__(1024) void act_quant_per_token(const half_t *__restrict__ x,
+                                                            int8_t *__restrict__ xq,
+                                                            half_t *__restrict__ xs, int K)
 {
-    __shared__ float red[4];
+    __shared__ float red[16];
     const int m = blockIdx.x;
     const h8 *row = (const h8 *)(x + (size_t)m * K);
     const int nvec = K / 8;
-    float amax = 0.0f;
-    for (int v = threadIdx.x; v < nvec; v += 256) {
-        h8 d = row[v];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf((float)d[i]));
-    }
-    amax = wave_max(amax);
+    u16x2 am = {0, 0};
+    for (int v = threadIdx.x; v < nvec; v += 1024) absmax8(row[v], am);
+    float amax = wave_max(absmax_of(am));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = amax;
     __syncthreads();
-    amax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+#pragma unroll
+    for (int w = 0; w < 16; ++w) amax = fmaxf(amax, red[w]);
     half_t s16 = store_scale(amax / 127.0f);
-    float s = (float)s16;
+    const float s = (float)s16, r = recip(s);
     if (threadIdx.x == 0) xs[m] = s16;
     uint2 *out = (uint2 *)(xq + (size_t)m * K);
-    for (int v = threadIdx.x; v < nvec; v += 256) out[v] = quant8(row[v], s);
+    for (int v = threadIdx.x; v < nvec; v += 1024) out[v] = quant8(row[v], s, r);
 }
 
 // 16 lanes per quantization group of 128; a block covers 16 groups of one token.
@@ -117,14 +117,15 @@ __global__ __launch_bounds__(256) void act_quant_per_group(const half_t *__restr
     if (g >= ng) return;   // whole 16-lane groups leave together; no block barrier below
     const size_t off = (size_t)m * K + (size_t)g * G + (threadIdx.x & 15) * 8;
     h8 d = *(const h8 *)(x + off);
-    float amax = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf((float)d[i]));
+    u16x2 am = {0, 0};
+    absmax8(d, am);
+    float amax = absmax_of(am);
 #pragma unroll
     for (int o = 8; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 16));
     half_t s16 = store_scale(amax / 127.0f);
+    const float s = (float)s16;
     if ((threadIdx.x & 15) == 0) xs[(size_t)m * ng + g] = s16;
-    *(uint2 *)(xq + off) = quant8(d, (float)s16);
+    *(uint2 *)(xq + off) = quant8(d, s, recip(s));
 }
 
 int launch_check_fast_division(unsigned long long *mismatches, hipStream_t st)
@@ -138,15 +139,20 @@ int launch_quantize_activations(const mixllm_desc &d, const void *x, int8_t *xq,
 {
     if (d.M == 0) return hipSuccess;
     if (d.act_group == d.K) {
-        if (d.K <= 2048 * 2)
-            hipLaunchKernelGGL(act_quant_per_token_regs<2>, dim3(d.M), dim3(256), 0, st, (const half_t *)x, xq,
-                               (half_t *)xs, d.K);
-        else if (d.K <= 2048 * 8)
-            hipLaunchKernelGGL(act_quant_per_token_regs<8>, dim3(d.M), dim3(256), 0, st, (const half_t *)x, xq,
-                               (half_t *)xs, d.K);
-        else
-            hipLaunchKernelGGL(act_quant_per_token, dim3(d.M), dim3(256), 0, st, (const half_t *)x, xq,
-                               (half_t *)xs, d.K);
+        // A block as wide as its row: few tokens wait for one load instead of up to seven in a row
+        // (K = 14336, 16 tokens: 4.3 us in 256 threads, 3.1 in 1024; K = 28672: 9.8 in the form that reads
+        // the row twice, 4.4 here), many tokens are indifferent (K = 14336, 2048 tokens: 20.3 / 19.4) until
+        // the block has threads without work (K = 4096, 8192 tokens: 20.3 us in 256 threads, 33 in 1024).
+        // Before the packed maximum and the shorter rounding K = 14336 took 94 us at 8192 tokens, now 65
+        // (5.4 TB/s), and 25 at 2048, now 19.
+        auto go = [&](auto kernel, int threads) {
+            hipLaunchKernelGGL(kernel, dim3(d.M), dim3(threads), 0, st, (const half_t *)x, xq, (half_t *)xs, d.K);
+        };
+        if (d.K <= 4096) go(act_quant_per_token_regs<2, 256>, 256);
+        else if (d.K <= 8192) go(act_quant_per_token_regs<2, 512>, 512);
+        else if (d.K <= 16384) go(act_quant_per_token_regs<2, 1024>, 1024);
+        else if (d.K <= 32768) go(act_quant_per_token_regs<4, 1024>, 1024);
+        else go(act_quant_per_token, 1024);
     } else {
         const int ng = d.K / G;
         hipLaunchKernelGGL(act_quant_per_group, dim3(d.M, (ng + 15) / 16), dim3(256), 0, st,

@@ -7,8 +7,6 @@
 
 namespace mixllm {
 
-typedef half_t h8 __attribute__((ext_vector_type(8)));
-
 // ------------------------------------------------- order of the concatenated rows --
 // feature_perm from a DEVICE list of the 8-bit channels (Sec. 3.4: the two parts own different
 // channel indices; Alg. 1's per-layer slice arrives on the device from mixllm_select_salient):
@@ -151,16 +149,6 @@ int launch_build_feature_perm(int N, int n8, const int32_t *salient_idx_dev, int
 
 constexpr int QP_THREADS = 512, QP_WAVES = QP_THREADS / 64;
 
-// round(v / s) half to even for 16 values as the low bits of (round(v / s) + 1.5 * 2^23), the fp32
-// number whose mantissa holds the integer: the addition rounds exactly as rint does once the quotient
-// is clamped to whole limits, and replaces rint, a conversion and a mask.
-static __device__ inline uint32_t rounded_bits(half_t v, float s, float r, float lo, float hi)
-{
-    const float t = __builtin_amdgcn_fmed3f(quotient((float)v, s, r), lo, hi);
-    return __builtin_bit_cast(uint32_t, t + 12582912.0f);
-}
-constexpr uint32_t ROUND_BIAS = 0x4B400000u;   // bits of 1.5 * 2^23
-
 static __device__ inline void absmax16(const h8 &a, const h8 &b, float &amax)
 {
 #pragma unroll
@@ -173,9 +161,8 @@ static __device__ inline uint4 codes8x16(const h8 &a, const h8 &b, float s, floa
     for (int d = 0; d < 4; ++d) {
         uint32_t v[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = rounded_bits(d < 2 ? a[4 * d + i] : b[4 * (d - 2) + i], s, r, -127.0f, 127.0f);
-        // the low byte of each
-        w[d] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(v[3], v[2], 0x0c0c0400u), __builtin_amdgcn_perm(v[1], v[0], 0x0c0c0400u), 0x05040100u);
+        for (int i = 0; i < 4; ++i) v[i] = quant_bits(d < 2 ? a[4 * d + i] : b[4 * (d - 2) + i], s, r);
+        w[d] = pack_low_bytes(v[0], v[1], v[2], v[3]);
     }
     return make_uint4(w[0], w[1], w[2], w[3]);
 }

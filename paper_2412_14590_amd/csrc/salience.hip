@@ -11,8 +11,6 @@ namespace mixllm {
 
 namespace {
 
-typedef half_t h8 __attribute__((ext_vector_type(8)));
-
 // ---- channel salience -------------------------------------------------------------------
 // One block of 4 waves per output channel.  A wave-wide 16-byte load covers 4 quantization
 // groups (16 lanes x 8 values each); the group's range, scale and zero point are found inside
