@@ -144,6 +144,45 @@ static inline __device__ uint2 quant8(const h8 &v, float s, float r)
     for (int i = 0; i < 8; ++i) b[i] = quant_bits(v[i], s, r);
     return make_uint2(pack_low_bytes(b[0], b[1], b[2], b[3]), pack_low_bytes(b[4], b[5], b[6], b[7]));
 }
+// largest magnitude of 8 values, folded into a pair of running maxima: fp16 magnitudes order like
+// their bit patterns, so the maximum is a packed one of 16-bit integers (one instruction per value
+// with the mask; a conversion and an fp32 maximum each took two)
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+static inline __device__ void absmax8(const h8 &v, u16x2 &m)
+{
+    const uint4 w = __builtin_bit_cast(uint4, v);
+    const uint32_t d[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, d[i] & 0x7fff7fffu));
+}
+static inline __device__ float absmax_of(u16x2 m)
+{
+    return (float)__builtin_bit_cast(half_t, (uint16_t)max(m.x, m.y));
+}
+// maximum of a non-negative float (its bit pattern orders like it) over every run of 16 lanes / over the wave,
+// all lanes active: rotations inside a row of 16 lanes cost an instruction each where a shuffle is a trip
+// through the LDS (about 60 ns), six of them in a row in front of everything a decode block does
+template <int CTRL>
+static inline __device__ uint32_t max_dpp(uint32_t v)
+{
+    return max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true));
+}
+static inline __device__ float row16_max(float f)
+{
+    uint32_t v = __builtin_bit_cast(uint32_t, f);
+    v = max_dpp<0x121>(v);   // row_ror:1, 2, 4, 8
+    v = max_dpp<0x122>(v);
+    v = max_dpp<0x124>(v);
+    v = max_dpp<0x128>(v);
+    return __builtin_bit_cast(float, v);
+}
+static inline __device__ float wave_max(float f)
+{
+    const int v = __builtin_bit_cast(int, row16_max(f));
+    const uint32_t a = max((uint32_t)__builtin_amdgcn_readlane(v, 0), (uint32_t)__builtin_amdgcn_readlane(v, 16));
+    const uint32_t b = max((uint32_t)__builtin_amdgcn_readlane(v, 32), (uint32_t)__builtin_amdgcn_readlane(v, 48));
+    return __builtin_bit_cast(float, max(a, b));
+}
 // one int8 code with the IEEE division (the reference of the exhaustive check)
 static inline __device__ uint32_t quant_code_ieee(half_t v, float s)
 {

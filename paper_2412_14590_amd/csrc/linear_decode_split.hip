@@ -327,11 +327,9 @@ __device__ inline void split_block(const LinearParams &p, const SplitArgs &a, ui
             const int i = tid + NT * j;
             if (j * NT < npiece) {
                 const h8 hv = __builtin_bit_cast(h8, xv[j]);   // the whole register, after its wait
-                float amax = 0.0f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf((float)hv[e]));
-#pragma unroll
-                for (int o = 8; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+                u16x2 am = {0, 0};
+                absmax8(hv, am);
+                const float amax = row16_max(absmax_of(am));
                 const float sc = (float)store_scale(amax / 127.0f);
                 const float rc = recip(sc);
                 const uint2 codes = quant8(hv, sc, rc);
@@ -352,11 +350,9 @@ __device__ inline void split_block(const LinearParams &p, const SplitArgs &a, ui
             const int i0 = wave * 64 + NT * j;   // first piece of the wave's load j
             if (j * NT < npiece && i0 < npiece) {
                 const h8 hv = __builtin_bit_cast(h8, xv[j]);   // the whole register, after its wait
-                float amax = 0.0f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf((float)hv[e]));
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+                u16x2 am = {0, 0};
+                absmax8(hv, am);
+                const float amax = wave_max(absmax_of(am));
                 if (lane == 0) atomicMax(&tokmax[i0 / per_row], __builtin_bit_cast(uint32_t, amax));
             }
         }
@@ -380,17 +376,11 @@ __device__ inline void split_block(const LinearParams &p, const SplitArgs &a, ui
         }
     } else if (FUSED == 1) {
         // one token: row maximum over all threads, then the codes
-        float amax = 0.0f;
+        u16x2 am = {0, 0};
 #pragma unroll
-        for (int j = 0; j < MAXV; ++j) {
-            if (j * NT < npiece && tid + NT * j < npiece) {
-                const h8 hv = __builtin_bit_cast(h8, xv[j]);   // the whole register, after its wait
-#pragma unroll
-                for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf((float)hv[e]));
-            }
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+        for (int j = 0; j < MAXV; ++j)
+            if (j * NT < npiece && tid + NT * j < npiece) absmax8(__builtin_bit_cast(h8, xv[j]), am);   // the whole register, after its wait
+        const float amax = wave_max(absmax_of(am));
         if (lane == 0) wmax[wave] = amax;
         lds_barrier();
         float rowmax = 0.0f;

@@ -5,29 +5,6 @@
 
 namespace mixllm {
 
-static __device__ inline float wave_max(float v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-    return v;
-}
-
-// largest magnitude of 8 values, folded into a pair of running maxima: fp16 magnitudes order like
-// their bit patterns, so the maximum is a packed one of 16-bit integers (one instruction per value
-// with the mask; a conversion and an fp32 maximum each took two)
-typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-static __device__ inline void absmax8(const h8 &v, u16x2 &m)
-{
-    const uint4 w = __builtin_bit_cast(uint4, v);
-    const uint32_t d[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, d[i] & 0x7fff7fffu));
-}
-static __device__ inline float absmax_of(u16x2 m)
-{
-    return (float)__builtin_bit_cast(half_t, (uint16_t)max(m.x, m.y));
-}
-
 // Exhaustive check of quotient(): for every positive finite fp16 scale (one block each) and every
 // finite fp16 value the int8 code from quotient() against the code from the IEEE division.
 __global__ __launch_bounds__(256) void check_fast_division_kernel(unsigned long long *mismatches)
@@ -119,9 +96,7 @@ __global__ __launch_bounds__(256) void act_quant_per_group(const half_t *__restr
     h8 d = *(const h8 *)(x + off);
     u16x2 am = {0, 0};
     absmax8(d, am);
-    float amax = absmax_of(am);
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 16));
+    const float amax = row16_max(absmax_of(am));
     half_t s16 = store_scale(amax / 127.0f);
     const float s = (float)s16;
     if ((threadIdx.x & 15) == 0) xs[(size_t)m * ng + g] = s16;
