@@ -26,7 +26,7 @@
 //    block-wide barrier sits in the middle of a group (slot TM*2), where the next group's
 //    activations are known to have landed and the stage of the previous group is released.
 //  * Group metadata (4 fp16 scales, 4 zero points) is fetched once per 4 groups.
-//  * Epilogue: token scale (all of a lane's scales requested by hand in one batch), fp16
+//  * Epilogue: token scale (from LDS, where the prologue left the block's), fp16
 //    conversion, scatter to the original channel (Sec. 3.4).
 // 8-bit and 4-bit channel tiles are different block ranges of one launch; where the grid of output
 // tiles is short and K long, K is split over blocks and a second kernel adds the parts.
@@ -361,30 +361,13 @@ static __device__ inline void prefill_block(const LinearParams &p, int m0, int t
         load_reg_u16(sa_bits, sa_voff, p.xscale + min(g_lo + 1, g_hi - 1));
     }
     const float sw_row = (PART8 && DUMP != 1 && !PG8) ? (float)p.s8[rw] : 0.0f;
-    // Token scales of the epilogue (one per token): all 16 TM of a lane are requested together, by
-    // hand, ahead of the epilogue - in the prologue where the registers allow it (the epilogue of a
-    // short launch otherwise pays a round trip to memory for them), else after the K loop and its
-    // drain: one round trip for all of them.  (Written as plain loads inside the
-    // epilogue they cost one round trip per token tile: the compiler does not move the next
-    // tile's loads above the stores of the previous one.)
-    constexpr bool HAND_SA = ACT_PT && DUMP == 0, EARLY_SA = HAND_SA && TM <= 2;
-    uint32_t sa_ep[HAND_SA ? TM : 1][16];
-    auto request_token_scales = [&]() {
-#pragma unroll
-        for (int mt = 0; mt < TM; ++mt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                load_reg_u16(sa_ep[mt][r], (uint32_t)min(m0 + mw0 + mt * 32 + 8 * (r >> 2) + 4 * h + (r & 3), p.M - 1) * 2u, p.xscale);
-    };
-    auto await_token_scales = [&]() {
-#pragma unroll
-        for (int mt = 0; mt < TM; ++mt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) await_loads<0>(sa_ep[mt][r]);
-    };
-    if constexpr (EARLY_SA) request_token_scales();
+    // Token scales of the epilogue (one per token): every thread fetches one and leaves it in LDS, where
+    // the epilogue finds the 16 TM a lane needs by 4 TM wide reads.  (Requested by each lane from
+    // memory, they were 16 TM two-byte loads per wave: 1.8 us of the 43 us a 128 x 128 block lives.)
+    constexpr bool TOKEN_SCALES = ACT_PT && DUMP == 0;
+    if constexpr (TOKEN_SCALES)
+        if (tid < BM) lds_sa[tid] = (float)p.xscale[min(m0 + tid, p.M - 1)];
     // everything above has landed (registers and LDS)
-    if constexpr (EARLY_SA) await_token_scales();
     await_loads<0>(meta_cur.s, meta_cur.z);
     await_loads<0>(sa_bits);
     if constexpr (PART8)
@@ -536,10 +519,6 @@ static __device__ inline void prefill_block(const LinearParams &p, int m0, int t
     static_for<0, NBUF>([&](auto sc) { await_loads<0>(b[decltype(sc)::value][0], b[decltype(sc)::value][1], b[decltype(sc)::value][2], b[decltype(sc)::value][3]); });
     await_loads<0>(meta_nxt.s, meta_nxt.z);
     await_loads<0>(sa_bits);
-    if constexpr (HAND_SA && !EARLY_SA) {   // (operand and int32 accumulator registers are free now)
-        request_token_scales();
-        await_token_scales();
-    }
     MIXLLM_STAMP(3);
     if (DUMP == 1) return;
     if (DUMP == 2) {
@@ -572,21 +551,16 @@ static __device__ inline void prefill_block(const LinearParams &p, int m0, int t
         return;
     }
     // ---- epilogue: token scale, fp16, scatter (Sec. 3.4) ------------------------------
-    // per token tile: the 16 token scales of the lane's rows are fetched together (clamped,
-    // unconditional) so that the loads overlap instead of costing one round trip per row
 #pragma unroll
     for (int mt = 0; mt < TM; ++mt) {
-        float sa[16];
+        v4f sa[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            sa[j] = TOKEN_SCALES ? *(const v4f *)(lds_sa + mw0 + mt * 32 + 8 * j + 4 * h) : v4f{1.0f, 1.0f, 1.0f, 1.0f};
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int m = m0 + mw0 + mt * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-            if constexpr (HAND_SA) sa[r] = half_bits_to_float(sa_ep[mt][r]);
-            else sa[r] = ACT_PT ? (float)p.xscale[min(m, p.M - 1)] : 1.0f;
-        }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int m = m0 + mw0 + mt * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-            if (m < p.M && ch >= 0) p.y[(size_t)m * p.N + ch] = (half_t)(acc[mt][r] * sa[r]);
+            if (m < p.M && ch >= 0) p.y[(size_t)m * p.N + ch] = (half_t)(acc[mt][r] * sa[r >> 2][r & 3]);
         }
     }
 }
@@ -650,26 +624,8 @@ static __device__ inline void prefill_block_w8_channel_scale(const LinearParams 
     static_assert(ACT_PT, "an integer sum over groups needs an activation scale that does not depend on the group");
     static_assert(DUMP != 1, "one accumulator over all of K: there is no per-group partial to dump");
     const float sw_row = (float)p.s8[rw];
-    // token scales of the epilogue, requested by hand ahead of it (see prefill_block)
-    constexpr bool HAND_SA = DUMP == 0, EARLY_SA = HAND_SA && TM <= 2;
-    uint32_t sa_ep[HAND_SA ? TM : 1][16];
-    auto request_token_scales = [&]() {
-#pragma unroll
-        for (int mt = 0; mt < TM; ++mt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                load_reg_u16(sa_ep[mt][r], (uint32_t)min(m0 + mw0 + mt * 32 + 8 * (r >> 2) + 4 * h + (r & 3), p.M - 1) * 2u, p.xscale);
-    };
-    auto await_token_scales = [&]() {
-#pragma unroll
-        for (int mt = 0; mt < TM; ++mt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) await_loads<0>(sa_ep[mt][r]);
-    };
-    if constexpr (EARLY_SA) {
-        request_token_scales();
-        await_token_scales();
-    }
+    // token scales of the epilogue (see prefill_block)
+    if (DUMP == 0 && tid < BM) lds_sa[tid] = (float)p.xscale[min(m0 + tid, p.M - 1)];
     static_for<0, L8>([&](auto sc) { await_loads<0>(b[decltype(sc)::value][0], b[decltype(sc)::value][1], b[decltype(sc)::value][2], b[decltype(sc)::value][3]); });
     __syncthreads();
     v4i af[RING];
@@ -727,10 +683,6 @@ static __device__ inline void prefill_block_w8_channel_scale(const LinearParams 
     }
     // drain (see prefill_block): nothing in flight towards this block's LDS or registers
     static_for<0, NBUF>([&](auto sc) { await_loads<0>(b[decltype(sc)::value][0], b[decltype(sc)::value][1], b[decltype(sc)::value][2], b[decltype(sc)::value][3]); });
-    if constexpr (HAND_SA && !EARLY_SA) {   // (the operand registers are free now)
-        request_token_scales();
-        await_token_scales();
-    }
 
     if (DUMP == 0 && p.kparts > 1) {   // K split over several blocks: see prefill_block
         const bool valid = t16 < p.ntiles8;
@@ -745,19 +697,16 @@ static __device__ inline void prefill_block_w8_channel_scale(const LinearParams 
     }
 #pragma unroll
     for (int mt = 0; mt < TM; ++mt) {
-        float sa[16];
+        v4f sa[4];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int m = m0 + mw0 + mt * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-            if constexpr (HAND_SA) sa[r] = half_bits_to_float(sa_ep[mt][r]);
-            else sa[r] = (float)p.xscale[min(m, p.M - 1)];
-        }
+        for (int j = 0; j < 4; ++j)
+            sa[j] = DUMP == 0 ? *(const v4f *)(lds_sa + mw0 + mt * 32 + 8 * j + 4 * h) : v4f{1.0f, 1.0f, 1.0f, 1.0f};
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int m = m0 + mw0 + mt * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
             if (DUMP == 2) {
                 if (m < p.M && ch >= 0) p.S[(size_t)m * p.N + ch] = P[mt][r];
-            } else if (m < p.M && ch >= 0) p.y[(size_t)m * p.N + ch] = (half_t)((float)P[mt][r] * sw_row * sa[r]);
+            } else if (m < p.M && ch >= 0) p.y[(size_t)m * p.N + ch] = (half_t)((float)P[mt][r] * sw_row * sa[r >> 2][r & 3]);
         }
     }
 }
@@ -770,8 +719,8 @@ __global__ __launch_bounds__(C::THREADS, MINW) void linear_prefill_kernel(Linear
     MIXLLM_STAMP(0);
     const int kp = blockIdx.y;
     const int g_lo = kp * p.quads_per_part * 4, g_hi = min(p.ng, g_lo + p.quads_per_part * 4);
-    // dynamic LDS (more than the 64 KB a static array may take): the activation stages, then
-    // the per-(token, group) activation scales when they are in use
+    // dynamic LDS (more than the 64 KB a static array may take): the activation stages, then the
+    // activation scales (one per token, or NSTAGE groups' per token)
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     uint8_t *lds_a = smem;
     float *lds_sa = (float *)(smem + NSTAGE * C::A_STAGE);
@@ -875,7 +824,7 @@ template <typename C, typename K>
 static int launch_variant(K kernel, bool with_sa, dim3 grid, dim3 block, hipStream_t st, const LinearParams &p, int nbm4,
                           int nbm8, int nb8, int nb4, int per4, int per8, int band4, int band8, int half8)
 {
-    const size_t lds_bytes = (size_t)NSTAGE * C::A_STAGE + (with_sa ? (size_t)NSTAGE * C::BM * sizeof(float) : 16);
+    const size_t lds_bytes = (size_t)NSTAGE * C::A_STAGE + (with_sa ? (size_t)NSTAGE : 1) * C::BM * sizeof(float);
     // (kernel, device) pairs already configured; a handful of instantiations exist
     struct Done {
         const void *fn;
@@ -1115,7 +1064,7 @@ bool prefill_plan(const LinearParams &p, int out[13])
     out[4] = g.nb4;
     out[5] = (g.per4 + g.per8) * 8;
     out[6] = g.band4;
-    out[7] = NSTAGE * BM * G + ((!p.act_per_token && !p.P) ? NSTAGE * BM * (int)sizeof(float) : 16);   // (p.P is never set here)
+    out[7] = NSTAGE * BM * G + ((!p.act_per_token && !p.P) ? NSTAGE : 1) * BM * (int)sizeof(float);   // (p.P is never set here)
     int qpp;
     out[8] = choose_kparts(p, tm, ~(size_t)0, qpp);   // blocks sharing a K range when the caller brings the scratch for it
     out[9] = 4 * qpp;                                 // quantization groups per part
