@@ -122,7 +122,9 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    # the current stream of the current device as an integer: the same value as
+    # torch.cuda.current_stream().cuda_stream without the Stream object made around it
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 @dataclass
@@ -218,8 +220,8 @@ def quantize_activations(x: torch.Tensor, act_group=None, out=None):
     M, K = x.shape
     act_group = K if act_group is None else act_group
     if out is None:
-        xq = torch.empty((M, K), dtype=torch.int8, device=x.device)
-        xs = torch.empty((M, K // act_group), dtype=torch.float16, device=x.device)
+        xq = x.new_empty((M, K), dtype=torch.int8)
+        xs = x.new_empty((M, K // act_group))
     else:
         xq, xs = out
     d = _desc(M, K, 1, 0, act_group, None)
@@ -234,7 +236,7 @@ def mixed_linear(xq: torch.Tensor, xs: torch.Tensor, L: PackedLayer, path: int =
     M, K = xq.shape
     assert K == L.K and xs.shape[0] == M
     act_group = K // xs.shape[1]
-    y = torch.empty((M, L.N), dtype=torch.float16, device=xq.device) if out is None else out
+    y = xq.new_empty((M, L.N), dtype=torch.float16) if out is None else out
     d = L.desc(M, act_group)
     wb = 0 if workspace is None else workspace.numel()
     _check(lib().mixllm_mixed_linear_path(C.byref(d), _ptr(xq), _ptr(xs), _ptr(L.w4), _ptr(L.w8), _ptr(L.s4),
@@ -281,11 +283,15 @@ def linear_fp16(x: torch.Tensor, L: PackedLayer, act_group=None, out=None, works
     M, K = x.shape
     assert K == L.K
     d = L.desc(M, act_group)
-    y = torch.empty((M, L.N), dtype=torch.float16, device=x.device) if out is None else out
-    need = query_sizes(M, K, L.N, L.n8, act_group, L.w8_group)["workspace_bytes"]
+    y = x.new_empty((M, L.N)) if out is None else out
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
-    wb = 0 if workspace is None else workspace.numel()
+        # asked with the descriptor at hand, one field read.  A token through the four linears of the 8B block
+        # was bound by the host (51 us, the kernels 39): this query, the stream's Python object and the
+        # allocations' keyword arguments were 4.4 of the 13 us of a call; 35 us without them
+        s = _Sizes()
+        _check(lib().mixllm_query_sizes(C.byref(d), C.byref(s)), "mixllm_query_sizes")
+        workspace = x.new_empty(s.workspace_bytes, dtype=torch.uint8)
+    wb = workspace.numel()
     _check(lib().mixllm_mixed_linear_fp16(C.byref(d), _ptr(x), _ptr(L.w4), _ptr(L.w8), _ptr(L.s4), _ptr(L.s8),
                                           _ptr(L.z4), _ptr(L.perm), _ptr(y), _ptr(workspace), wb, _stream()),
            "mixllm_mixed_linear_fp16")

@@ -444,6 +444,33 @@ def test_fused_quantizer_and_linear_from_fp16(M, K, N, n8, variant):
         assert torch.equal(y, y2)
 
 
+@pytest.mark.parametrize("path", ["prefill32", "prefill64", "prefill128"])
+@pytest.mark.parametrize("rows", [-1, 0, 1])
+@pytest.mark.parametrize("K,groups", [(640, False), (640, True), (8192, False)])
+def test_tiled_stores_at_the_last_token_tile(path, rows, K, groups):
+    # a last tile that is one row short, full, and one row over, of every block shape; K = 8192 with scratch,
+    # so that the parts of a K split go through the same stores; nothing is written past the last row
+    tile = int(path[len("prefill"):])
+    M, N, n8 = tile + rows, 150, 21
+    act_group = 128 if groups and path != "prefill128" else None
+    _, _, L, x, xq, xs = make_case(M, K, N, n8, seed=tile + rows, w8_group=128 if groups else None, act_group=act_group)
+    PL = pack_from_oracle(L)
+    need = mx.query_sizes(M, K, N, n8, act_group, L.w8_group)["linear_workspace_bytes"]
+    ws = torch.full((max(need, 4 * (1 << 20)) + 256,), 77, dtype=torch.uint8, device="cuda") if K >= 8192 else None
+    buf = torch.full((M * N + 64,), -3.0, dtype=torch.float16, device="cuda")
+    y = mx.mixed_linear(dev(xq), dev(xs), PL, PATHS[path], out=buf[: M * N].view(M, N), workspace=None if ws is None else ws[:-256])
+    check_against_oracle(y.cpu().numpy(), xq, xs, L, f"{path} M={M} K={K}")
+    assert bool((buf[M * N:] == -3.0).all())
+    assert ws is None or bool((ws[-256:] == 77).all())
+
+
+def test_calls_go_to_the_current_stream():
+    from paper_2412_14590_amd import binding
+    for s in (torch.cuda.default_stream(), torch.cuda.Stream(), torch.cuda.Stream()):
+        with torch.cuda.stream(s):
+            assert binding._stream() == torch.cuda.current_stream().cuda_stream == s.cuda_stream
+
+
 def test_fused_entry_point_rejects_a_short_workspace():
     W, sal, L, x, xq, xs = make_case(40, 512, 64, 6, seed=32)
     PL = pack_from_oracle(L)
