@@ -139,13 +139,12 @@ int launch_build_feature_perm(int N, int n8, const int32_t *salient_idx_dev, int
 }
 
 // ------------------------------------------------------------------ quantize + pack --
-// Bound by HBM: two bytes in, half a byte (or one) out per weight.  The lanes of a wave are the lanes
-// of the packed layout, lane = row of the tile + 16 * k-slot: a wave reads 16 rows x 256 bytes of one
-// group and writes the group's packed block as one contiguous KB.  (One block per row, the first
-// form, wrote 4-byte pieces 256 bytes apart, and the 16 rows that share a line ran on different
-// XCDs: 88 us for the 300 MB of K = 4096, N = 28672; this form 70, 4.3 TB/s.)
-// A unit of work is one tile of 16 rows x 8 groups, so that a row's metadata leaves as one 16-byte
-// (scales) and one 4-byte (zero points) store and the padding to a multiple of 8 groups falls out.
+// Bound by HBM: two bytes in, half a byte (or one) out per weight.  The lanes of a wave are lanes of the
+// packed layout: lane = row of the tile + 16 * k-slot, a wave reads 16 rows x 256 bytes of one group and writes
+// the group's packed block as one contiguous KB (one block per row, writing 4-byte pieces 256 bytes apart,
+// took 88 us for the 300 MB of K = 4096, N = 28672; this form 58).  Two things make a short launch longer than its
+// bytes: blocks that walk too much in sequence and too few of them, hence the second form of the 8-bit part
+// and the two sizes of a unit of the 4-bit part (rules at the launch).
 
 constexpr int QP_THREADS = 512, QP_WAVES = QP_THREADS / 64;
 
@@ -167,109 +166,192 @@ static __device__ inline uint4 codes8x16(const h8 &a, const h8 &b, float s, floa
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// blocks [0, n8p / 16): one tile of 16 8-bit rows each; the others: QP_WAVES units of the 4-bit part each
-__global__ __launch_bounds__(QP_THREADS) void quantize_pack_kernel(
-    const half_t *__restrict__ W, const int32_t *__restrict__ perm, int K, int n8, int n4, int n8p, int n4p,
-    int ng, int ngp, int w8_per_channel, int8_t *__restrict__ w8, uint8_t *__restrict__ w4,
-    half_t *__restrict__ s8, half_t *__restrict__ s4, uint8_t *__restrict__ z4)
+// One tile of 16 8-bit rows.  One scale per channel: each wave finds the maxima of two rows, the second read
+// of the tile comes from the L2; then every wave takes every QP_WAVES-th group.
+static __device__ inline void quantize_tile8(const half_t *__restrict__ W, const int32_t *__restrict__ perm, int K, int n8, int ng, int ngp,
+                                             int w8_per_channel, int block, int8_t *__restrict__ w8, half_t *__restrict__ s8, float *row_scale)
 {
-    __shared__ float row_scale[TILE_N];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int r16 = lane & 15, ks = lane >> 4;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r16 = lane & 15, ks = lane >> 4;
     const h8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
-    if ((int)blockIdx.x < n8p / TILE_N) {
-        // ---- a tile of 8-bit rows: (one scale per channel: each wave finds the maxima of two rows, the
-        //      second read of the tile comes from the L2), then every wave takes every QP_WAVES-th group
-        const int r0 = blockIdx.x * TILE_N;
-        if (w8_per_channel) {
-            for (int i = wave; i < TILE_N; i += QP_WAVES) {
-                const bool real = r0 + i < n8;
-                float amax = 0.0f;
-                if (real) {
-                    const half_t *row = W + (size_t)perm[r0 + i] * K;
-                    for (int k = lane * 16; k < K; k += 1024) absmax16(*(const h8 *)(row + k), *(const h8 *)(row + k + 8), amax);
-                }
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
-                if (lane == 0) {
-                    const half_t s16 = real ? store_scale(amax / 127.0f) : (half_t)0.0f;
-                    s8[r0 + i] = s16;
-                    row_scale[i] = (float)s16;
-                }
-            }
-            __syncthreads();
-        }
-        const int r = r0 + r16;
-        const bool real = r < n8;
-        const half_t *row = W + (size_t)(real ? perm[r] : 0) * K;
-        float s = w8_per_channel ? row_scale[r16] : 0.0f, rs = recip(s);
-        uint4 *out = (uint4 *)w8 + (size_t)blockIdx.x * (K / 64) * 64 + lane;
-        for (int g = wave; g < (w8_per_channel ? ng : ngp); g += QP_WAVES) {
-            if (g >= ng) {   // padding of the per-group scales
-                if (ks == 0) s8[(size_t)r * ngp + g] = (half_t)0.0f;
-                continue;
-            }
-            const half_t *src = row + g * G + ks * 16;   // 16 values in each half of the group
-            h8 v[4] = {zero8, zero8, zero8, zero8};
+    const int r0 = block * TILE_N;
+    if (w8_per_channel) {
+        for (int i = wave; i < TILE_N; i += QP_WAVES) {
+            const bool real = r0 + i < n8;
+            float amax = 0.0f;
             if (real) {
-                v[0] = *(const h8 *)src;
-                v[1] = *(const h8 *)(src + 8);
-                v[2] = *(const h8 *)(src + 64);
-                v[3] = *(const h8 *)(src + 72);
+                const half_t *row = W + (size_t)perm[r0 + i] * K;
+                for (int k = lane * 16; k < K; k += 1024) absmax16(*(const h8 *)(row + k), *(const h8 *)(row + k + 8), amax);
             }
-            if (!w8_per_channel) {
-                float amax = 0.0f;
-                absmax16(v[0], v[1], amax);
-                absmax16(v[2], v[3], amax);
-                amax = fmaxf(amax, __shfl_xor(amax, 16, 64));
-                amax = fmaxf(amax, __shfl_xor(amax, 32, 64));
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+            if (lane == 0) {
                 const half_t s16 = real ? store_scale(amax / 127.0f) : (half_t)0.0f;
-                if (ks == 0) s8[(size_t)r * ngp + g] = s16;
+                s8[r0 + i] = s16;
+                row_scale[i] = (float)s16;
+            }
+        }
+        __syncthreads();
+    }
+    const int r = r0 + r16;
+    const bool real = r < n8;
+    const half_t *row = W + (size_t)(real ? perm[r] : 0) * K;
+    float s = w8_per_channel ? row_scale[r16] : 0.0f, rs = recip(s);
+    uint4 *out = (uint4 *)w8 + (size_t)block * (K / 64) * 64 + lane;
+    for (int g = wave; g < (w8_per_channel ? ng : ngp); g += QP_WAVES) {
+        if (g >= ng) {   // padding of the per-group scales
+            if (ks == 0) s8[(size_t)r * ngp + g] = (half_t)0.0f;
+            continue;
+        }
+        const half_t *src = row + g * G + ks * 16;   // 16 values in each half of the group
+        h8 v[4] = {zero8, zero8, zero8, zero8};
+        if (real) {
+            v[0] = *(const h8 *)src;
+            v[1] = *(const h8 *)(src + 8);
+            v[2] = *(const h8 *)(src + 64);
+            v[3] = *(const h8 *)(src + 72);
+        }
+        if (!w8_per_channel) {
+            float amax = 0.0f;
+            absmax16(v[0], v[1], amax);
+            absmax16(v[2], v[3], amax);
+            amax = fmaxf(amax, __shfl_xor(amax, 16, 64));
+            amax = fmaxf(amax, __shfl_xor(amax, 32, 64));
+            const half_t s16 = real ? store_scale(amax / 127.0f) : (half_t)0.0f;
+            if (ks == 0) s8[(size_t)r * ngp + g] = s16;
+            s = (float)s16;
+            rs = recip(s);
+        }
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf)
+            out[(size_t)(2 * g + hf) * 64] = real ? codes8x16(v[2 * hf], v[2 * hf + 1], s, rs) : make_uint4(0, 0, 0, 0);
+    }
+}
+
+// A block's 2^lr (at most 8) 8-bit rows, r0 and on, where there are too few tiles for the chip: lane = row + 2^lr * slot, a slot being 16
+// consecutive k, so that a load of a wave always holds whole groups of the rows it touches.  The waves take the
+// row's chunks (one load of a wave each) in turn, QP_AHEAD of them requested together.  With one scale per
+// channel the rows are walked twice (the second read comes from the L2 or the memory-side cache).
+constexpr int QP_AHEAD = 4;
+static __device__ inline void quantize_rows8(const half_t *__restrict__ W, const int32_t *__restrict__ perm, int K, int n8, int ng, int ngp,
+                                             int w8_per_channel, int r0, int lr, int8_t *__restrict__ w8, half_t *__restrict__ s8,
+                                             float *wave_max8)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int rows = 1 << lr, slot = lane >> lr, r = r0 + (lane & (rows - 1));
+    const bool real = r < n8;
+    const half_t *row = W + (size_t)perm[min(r, n8 - 1)] * K;   // (a row of the padding reads the last one; its codes and scales are zero)
+    const int nslots = K / 16, per = 64 >> lr, nchunks = (nslots + per - 1) / per;
+    // chunk c of this lane: the slot past the end re-reads the last one (it changes no maximum and is not stored)
+    auto load = [&](int c, h8 &a, h8 &b) {
+        const half_t *src = row + min(c * per + slot, nslots - 1) * 16;
+        a = *(const h8 *)src;
+        b = *(const h8 *)(src + 8);
+    };
+    float s = 0.0f;
+    if (w8_per_channel) {
+        float amax = 0.0f;
+        for (int c0 = wave; c0 < nchunks; c0 += QP_AHEAD * QP_WAVES) {
+            h8 a[QP_AHEAD], b[QP_AHEAD];
+#pragma unroll
+            for (int j = 0; j < QP_AHEAD; ++j) load(c0 + j * QP_WAVES, a[j], b[j]);
+#pragma unroll
+            for (int j = 0; j < QP_AHEAD; ++j) absmax16(a[j], b[j], amax);
+        }
+        for (int o = 32; o >= rows; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+        if (slot == 0) wave_max8[wave * 8 + lane] = amax;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < QP_WAVES; ++w) amax = fmaxf(amax, wave_max8[w * 8 + (lane & (rows - 1))]);
+        const half_t s16 = real ? store_scale(amax / 127.0f) : (half_t)0.0f;
+        if (tid < rows) s8[r] = s16;
+        s = (float)s16;
+    } else if (wave == 0) {
+        for (int g = ng + slot; g < ngp; g += per) s8[(size_t)r * ngp + g] = (half_t)0.0f;   // padding of the per-group scales
+    }
+    float rs = recip(s);
+    uint4 *out = (uint4 *)w8 + (size_t)(r / TILE_N) * (K / 64) * 64 + r % TILE_N;
+    for (int c0 = wave; c0 < nchunks; c0 += QP_AHEAD * QP_WAVES) {
+        h8 a[QP_AHEAD], b[QP_AHEAD];
+#pragma unroll
+        for (int j = 0; j < QP_AHEAD; ++j) load(c0 + j * QP_WAVES, a[j], b[j]);
+#pragma unroll
+        for (int j = 0; j < QP_AHEAD; ++j) {
+            const int q = (c0 + j * QP_WAVES) * per + slot;
+            if (!w8_per_channel) {   // the 8 slots of a group lie in 8 lanes of the same row (a group is valid as a whole)
+                float amax = 0.0f;
+                absmax16(a[j], b[j], amax);
+                for (int o = rows; o < 8 * rows; o <<= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+                const half_t s16 = real ? store_scale(amax / 127.0f) : (half_t)0.0f;
+                if (q < nslots && (slot & 7) == 0) s8[(size_t)r * ngp + (q >> 3)] = s16;
                 s = (float)s16;
                 rs = recip(s);
             }
-#pragma unroll
-            for (int hf = 0; hf < 2; ++hf)
-                out[(size_t)(2 * g + hf) * 64] = real ? codes8x16(v[2 * hf], v[2 * hf + 1], s, rs) : make_uint4(0, 0, 0, 0);
+            const uint4 codes = codes8x16(a[j], b[j], s, rs);
+            if (q < nslots) out[(size_t)(q >> 2) * 64 + 16 * (q & 3)] = real ? codes : make_uint4(0, 0, 0, 0);
         }
+    }
+}
+
+// blocks [0, nblk8): one tile of 8-bit rows each (TILE8), or 2^lr of them; the others: QP_WAVES units of the 4-bit part each, a unit being
+// one tile of 16 rows x U groups (U = 8 or 2; two groups are requested together)
+template <bool TILE8, int U>
+__global__ __launch_bounds__(QP_THREADS) void quantize_pack_kernel(
+    const half_t *__restrict__ W, const int32_t *__restrict__ perm, int K, int n8, int n4, int nblk8, int lr, int n4p,
+    int ng, int ngp, int w8_per_channel, int8_t *__restrict__ w8, uint8_t *__restrict__ w4,
+    half_t *__restrict__ s8, half_t *__restrict__ s4, uint8_t *__restrict__ z4)
+{
+    __shared__ float maxima[TILE8 ? TILE_N : QP_WAVES * 8];
+    if ((int)blockIdx.x < nblk8) {
+        if constexpr (TILE8) quantize_tile8(W, perm, K, n8, ng, ngp, w8_per_channel, blockIdx.x, w8, s8, maxima);
+        else quantize_rows8(W, perm, K, n8, ng, ngp, w8_per_channel, (int)blockIdx.x << lr, lr, w8, s8, maxima);
         return;
     }
-    // ---- a unit of the 4-bit part
-    const int upt = ngp / 8;   // units per tile
-    const int unit = ((int)blockIdx.x - n8p / TILE_N) * QP_WAVES + wave;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r16 = lane & 15, ks = lane >> 4;
+    const int upt = ngp / U;   // units per tile
+    const int unit = ((int)blockIdx.x - nblk8) * QP_WAVES + wave;
     if (unit >= n4p / TILE_N * upt) return;
-    const int tile = unit / upt, g0 = (unit - tile * upt) * 8;
+    const int tile = unit / upt, g0 = (unit - tile * upt) * U;
     const int r = tile * TILE_N + r16;
     const bool real = r < n4;
-    const half_t *row = W + (size_t)(real ? perm[n8 + r] : 0) * K + ks * 16;
+    const half_t *row = W + (size_t)perm[n8 + min(r, n4 - 1)] * K + ks * 16;   // (padding rows read the last one, see quantize_rows8)
     uint4 *out = (uint4 *)w4 + ((size_t)tile * ng + g0) * 64 + lane;
-    uint32_t scales[4] = {0, 0, 0, 0}, zeros = 0;
+    uint32_t scales[U / 2], zeros = 0;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        if (g0 + u >= ng) break;   // (the metadata of these padding groups is zero)
-        uint4 packed = make_uint4(0, 0, 0, 0);
-        half_t s16 = (half_t)0.0f;
-        int z = 0;
-        if (real) {
-            const half_t *src = row + (g0 + u) * G;
-            const h8 v[4] = {*(const h8 *)src, *(const h8 *)(src + 8), *(const h8 *)(src + 64), *(const h8 *)(src + 72)};
+    for (int i = 0; i < U / 2; ++i) scales[i] = 0;
+#pragma unroll
+    for (int u0 = 0; u0 < U; u0 += 2) {
+        if (g0 + u0 >= ng) break;   // (the metadata of these padding groups is zero)
+        h8 v[2][4];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const half_t *src = row + min(g0 + u0 + j, ng - 1) * G;
+            v[j][0] = *(const h8 *)src;
+            v[j][1] = *(const h8 *)(src + 8);
+            v[j][2] = *(const h8 *)(src + 64);
+            v[j][3] = *(const h8 *)(src + 72);
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int u = u0 + j;
+            if (g0 + u >= ng) break;
             float mn = 0.0f, mx = 0.0f;   // the range always contains 0
 #pragma unroll
             for (int d = 0; d < 4; ++d)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                    mn = fminf(mn, (float)v[d][i]);
-                    mx = fmaxf(mx, (float)v[d][i]);
+                    mn = fminf(mn, (float)v[j][d][i]);
+                    mx = fmaxf(mx, (float)v[j][d][i]);
                 }
 #pragma unroll
             for (int o = 16; o < 64; o <<= 1) {
                 mn = fminf(mn, __shfl_xor(mn, o, 64));
                 mx = fmaxf(mx, __shfl_xor(mx, o, 64));
             }
-            s16 = store_scale((mx - mn) / 15.0f);
+            const half_t s16 = store_scale((mx - mn) / 15.0f);
             const float sc = (float)s16, rsc = recip(sc);
             const float zf = fminf(fmaxf(__builtin_rintf(quotient(-mn, sc, rsc)), 0.0f), 15.0f);
-            z = (int)zf;
+            const int z = (int)zf;
             // code = clamp(round(v / s) + z, 0, 15), the limits moved to the other side of the sum; the
             // eight biases of a dword are taken off (and z added) in one addition modulo 2^32
             const uint32_t fix = ((uint32_t)z - ROUND_BIAS) * 0x11111111u;
@@ -279,17 +361,25 @@ __global__ __launch_bounds__(QP_THREADS) void quantize_pack_kernel(
                 w[d] = fix;
 #pragma unroll
                 for (int i = 0; i < 8; ++i)   // byte b of a dword: k-local b in the low nibble, b + 4 in the high one
-                    w[d] += rounded_bits(v[d][i], sc, rsc, -zf, 15.0f - zf) << (8 * (i & 3) + (i & 4));
+                    w[d] += rounded_bits(v[j][d][i], sc, rsc, -zf, 15.0f - zf) << (8 * (i & 3) + (i & 4));
             }
-            packed = make_uint4(w[0], w[1], w[2], w[3]);
+            out[u * 64] = real ? make_uint4(w[0], w[1], w[2], w[3]) : make_uint4(0, 0, 0, 0);
+            if (real) {
+                scales[u >> 1] |= (uint32_t)__builtin_bit_cast(uint16_t, s16) << (16 * (u & 1));
+                zeros |= (uint32_t)z << (4 * u);
+            }
         }
-        out[u * 64] = packed;
-        scales[u >> 1] |= (uint32_t)__builtin_bit_cast(uint16_t, s16) << (16 * (u & 1));
-        zeros |= (uint32_t)z << (4 * u);
     }
     if (ks == 0) {
-        *(uint4 *)(s4 + (size_t)r * ngp + g0) = make_uint4(scales[0], scales[1], scales[2], scales[3]);
-        *(uint32_t *)(z4 + (size_t)r * (ngp / 2) + g0 / 2) = zeros;
+        half_t *so = s4 + (size_t)r * ngp + g0;
+        uint8_t *zo = z4 + (size_t)r * (ngp / 2) + g0 / 2;
+        if constexpr (U == 8) {
+            *(uint4 *)so = make_uint4(scales[0], scales[1], scales[2], scales[3]);
+            *(uint32_t *)zo = zeros;
+        } else {
+            *(uint32_t *)so = scales[0];
+            *zo = (uint8_t)zeros;
+        }
     }
 }
 
@@ -299,10 +389,30 @@ int launch_quantize_weights(const mixllm_desc &d, const void *W, void *w8, void 
     const int n4 = d.N - d.n8, n8p = round_up(d.n8, TILE_N), n4p = round_up(n4, TILE_N);
     const int ng = d.K / G, ngp = round_up(ng, 8);
     if (n8p + n4p == 0) return hipSuccess;
-    const int units = n4p / TILE_N * (ngp / 8);
-    hipLaunchKernelGGL(quantize_pack_kernel, dim3(n8p / TILE_N + (units + QP_WAVES - 1) / QP_WAVES), dim3(QP_THREADS), 0, st,
-                       (const half_t *)W, perm, d.K, d.n8, n4, n8p, n4p, ng, ngp, d.w8_group == d.K ? 1 : 0, (int8_t *)w8,
-                       (uint8_t *)w4, (half_t *)s8, (half_t *)s4, (uint8_t *)z4);
+    // Rows of a block of the 8-bit part.  Its two passes over 2^lr rows are a chain, and a launch with few other blocks
+    // waits for it (one block per tile of 16 rows: K = 28672, N = 1024 with 102 8-bit channels 59 us, row order
+    // included, K = 131072, N = 64 with 32 of them 229; here 24 and 24): it is hidden while the rows are at most
+    // 1/600 of the layer's, and does not matter once the 8-bit blocks alone cover three quarters of the CUs; otherwise
+    // the rows are halved, down to one.  (8 / 4 / 2 / 1 rows, K = 28672: N = 1024 with 102 8-bit channels
+    // 49 / 34 / 22 / 23 us, with 1024 48 / 34 / 33 / 41, N = 8192 with 819 128 / 134 / 136 / 142; K = 4096, N = 6144
+    // with 614 20 / 20 / 22 / 24.)  Whole tiles where there is one per CU (K = 4096, N = 28672, all channels 8-bit, a scale
+    // per group: 102 us, in blocks of 8 rows 112) and on wide layers of short rows (K = 1152, N = 28672: 25, 30).
+    const int cus = cu_count();
+    const bool tile8 = n8p / TILE_N >= cus || (ng <= 16 && d.N >= 600 * TILE_N);
+    int lr = tile8 ? 4 : 3;
+    while (!tile8 && lr > 0 && 600 << lr > d.N && 4 * (n8p >> lr) < 3 * cus) --lr;
+    // Groups of a unit of the 4-bit part: 2, requested together (units of 8: K = 1152, N = 300 15 us, here 9, K = N = 4096
+    // 18.4, 14.5, K = 8192, N = 57344 263, 249), unless most of a row's units would be padding (K = 384, N = 28672 12.7 us, in
+    // units of 2 14.2; K = 128, N = 131072 17, 28).
+    const bool u8 = ng < 4;
+    const int units = n4p / TILE_N * (ngp / (u8 ? 8 : 2)), nblk8 = n8p >> lr;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(nblk8 + (units + QP_WAVES - 1) / QP_WAVES), dim3(QP_THREADS), 0, st, (const half_t *)W, perm,
+                           d.K, d.n8, n4, nblk8, lr, n4p, ng, ngp, d.w8_group == d.K ? 1 : 0, (int8_t *)w8, (uint8_t *)w4, (half_t *)s8,
+                           (half_t *)s4, (uint8_t *)z4);
+    };
+    if (tile8) u8 ? go(quantize_pack_kernel<true, 8>) : go(quantize_pack_kernel<true, 2>);
+    else u8 ? go(quantize_pack_kernel<false, 8>) : go(quantize_pack_kernel<false, 2>);
     return (int)hipGetLastError();
 }
 

@@ -185,6 +185,54 @@ def test_conversion_at_the_edges_of_tiles_and_units(K, N, n8, w8_group):
     assert torch.equal(q4[3:-29].view(N - n8, K), u["q4"]) and bool((q4[:3] == 99).all()) and bool((q4[-29:] == 99).all())
 
 
+@pytest.mark.parametrize("K,N,n8", [
+    (256, 9600, 50), (2048, 9600, 33), (1152, 9599, 33),         # whole tiles on wide layers of short rows, and one channel short of that
+    (384, 4200, 4081), (512, 4200, 4080),                        # 256 tiles of 8-bit rows and one fewer (units of 8 and of 2 groups)
+    (2176, 4800, 17), (2176, 4799, 17), (1152, 2400, 31), (1152, 2399, 16), (640, 1200, 15), (640, 1199, 15),   # 8, 4, 4, 2, 2, 1 rows a block
+    (512, 1100, 1090), (128, 400, 390), (16, 16, 16),            # rows by the number of blocks (K is times 128 in the last)
+    (33024, 20, 3), (32896, 20, 20),                             # more chunks of a row than are requested together
+])
+@pytest.mark.parametrize("w8_group", [None, 128])
+def test_weight_quantizer_in_every_block_shape(K, N, n8, w8_group):
+    # both forms of the 8-bit part, every height of its blocks and both units of the 4-bit part, with rows,
+    # groups and chunks that do not fill them; the packed buffers (padding included) are those of packing the oracle's codes
+    K = 128 * K if K < 128 else K
+    rng = np.random.default_rng(K + N)
+    W = (rng.standard_normal((N, K), dtype=np.float32) * 0.02).astype(np.float16)
+    W[rng.integers(0, N), K - 1] = 3.0                           # a maximum in the last value of a row
+    sal = rng.permutation(N)[:n8].astype(np.int32)
+    want = pack_from_oracle(ref.quantize_weights(W, sal, G, w8_group))
+    got = mx.quantize_weights(dev(W), dev(sal), w8_group)
+    for k in ("w8", "w4", "s8", "s4", "z4", "perm"):
+        assert torch.equal(getattr(want, k), getattr(got, k)), k
+
+
+def test_conversion_of_few_long_rows_takes_as_long_as_that_of_many_short_ones():
+    # the same number of weights and the same 8-bit share, 1024 rows of 28672 and 7168 of 4096, from a graph (a block per
+    # tile of 8-bit rows walked its 16 long rows in sequence: 56 us against 21; in blocks of fewer rows 22 against 20)
+    def us(N, K):
+        W = torch.randn((N, K), device="cuda", dtype=torch.float16) * 0.02
+        sal = torch.arange(0, N, 10, dtype=torch.int32, device="cuda")
+        mx.quantize_weights(W, sal)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(10):
+                mx.quantize_weights(W, sal)
+        times = []
+        for _ in range(9):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            graph.replay()
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b) * 100)
+        return sorted(times)[4]
+    narrow, wide = us(1024, 28672), us(7168, 4096)
+    say(f"weight conversion, 29.4 M weights: 1024 rows {narrow:.1f} us, 7168 rows {wide:.1f} us")
+    assert narrow < 1.6 * wide
+
+
 def test_a_bad_device_list_of_8bit_channels_never_writes_out_of_bounds():
     # indices out of range are ignored, duplicates count once; the order is then unspecified, but
     # every entry stays a channel number and the buffers around feature_perm are untouched
