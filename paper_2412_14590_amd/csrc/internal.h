@@ -145,19 +145,27 @@ static inline __device__ uint2 quant8(const h8 &v, float s, float r)
     return make_uint2(pack_low_bytes(b[0], b[1], b[2], b[3]), pack_low_bytes(b[4], b[5], b[6], b[7]));
 }
 // largest magnitude of 8 values, folded into a pair of running maxima: fp16 magnitudes order like
-// their bit patterns, so the maximum is a packed one of 16-bit integers (one instruction per value
-// with the mask; a conversion and an fp32 maximum each took two)
+// their bit patterns, so the maximum is a packed one of 16-bit integers (one instruction per value; a
+// conversion and an fp32 maximum each took two).  What is compared is 2 v + ABSMAX_BIAS modulo 2^16: the
+// doubling drops the sign, and the bias makes infinity the largest integer and moves the NaN patterns above
+// it past the end, below zero's: a NaN counts as nothing, as in fmaxf.
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+constexpr uint32_t ABSMAX_BIAS = 0xffff - 2 * 0x7c00;
 static inline __device__ void absmax8(const h8 &v, u16x2 &m)
 {
     const uint4 w = __builtin_bit_cast(uint4, v);
     const uint32_t d[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, d[i] & 0x7fff7fffu));
+    for (int i = 0; i < 4; ++i) {
+        u16x2 t;   // (the compiler makes a shift and an addition of it)
+        asm("v_pk_mad_u16 %0, %1, 2, %2 op_sel_hi:[1,0,1]" : "=v"(t) : "v"(d[i]), "s"(ABSMAX_BIAS * 0x10001u));
+        m = __builtin_elementwise_max(m, t);
+    }
 }
-static inline __device__ float absmax_of(u16x2 m)
+static inline __device__ float absmax_of(u16x2 m)   // (of {0, 0}, no values: zero)
 {
-    return (float)__builtin_bit_cast(half_t, (uint16_t)max(m.x, m.y));
+    const uint32_t b = max(m.x, m.y);
+    return (float)__builtin_bit_cast(half_t, (uint16_t)(b > ABSMAX_BIAS ? (b - ABSMAX_BIAS) >> 1 : 0));
 }
 // maximum of a non-negative float (its bit pattern orders like it) over every run of 16 lanes / over the wave,
 // all lanes active: rotations inside a row of 16 lanes cost an instruction each where a shuffle is a trip

@@ -233,6 +233,33 @@ def test_conversion_of_few_long_rows_takes_as_long_as_that_of_many_short_ones():
     assert narrow < 1.6 * wide
 
 
+@pytest.mark.parametrize("K", [512, 4096, 8192, 14336, 28672, 33024])
+@pytest.mark.parametrize("act_group", [None, 128])
+def test_a_nan_does_not_enter_the_scale_of_its_row(K, act_group):
+    # (unsupported input, but one bad value leaves its row's scale and the other codes alone, and every way through
+    # the library agrees: the stand-alone quantizer in all its block widths and the quantizers inside the decode kernels)
+    rng = np.random.default_rng(K)
+    x = synth.make_x(4, K, seed=K)
+    cols = np.array([3, K // 2 + 1, K - 1])
+    clean = x.copy()
+    clean[1:3, cols] = 0.0
+    x[1, cols] = np.nan
+    x.view(np.uint16)[2, cols] = [0xfe01, 0x7c01, 0xffff]        # negative, signalling, all bits
+    x[3, rng.integers(0, K)] = clean[3].max() * 2
+    clean[3] = x[3]
+    xq_ref, xs_ref = ref.quantize_act(clean, act_group)
+    xq_ref[1:3, cols] = -127                                     # what clamping a NaN to [-127, 127] gives
+    xq, xs = mx.quantize_activations(dev(x), act_group)
+    assert np.array_equal(xs.cpu().numpy().view(np.uint16), xs_ref.view(np.uint16))
+    assert np.array_equal(xq.cpu().numpy(), xq_ref)
+    W = synth.make_w(40, K, seed=1, n_outlier_rows=1)
+    PL = mx.quantize_weights(dev(W), np.arange(4, dtype=np.int32))
+    for rows in ([1], [2, 3], [0, 1, 2, 3]):
+        y = mx.linear_fp16(dev(x[rows]), PL, act_group)
+        two = mx.mixed_linear(dev(xq_ref[rows]), dev(xs_ref[rows]), PL)
+        assert torch.isfinite(y).all() and row_rel_err(y.cpu().numpy(), two.cpu().numpy()) <= TOL
+
+
 def test_a_bad_device_list_of_8bit_channels_never_writes_out_of_bounds():
     # indices out of range are ignored, duplicates count once; the order is then unspecified, but
     # every entry stays a channel number and the buffers around feature_perm are untouched
