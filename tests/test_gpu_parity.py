@@ -233,6 +233,21 @@ def test_conversion_of_few_long_rows_takes_as_long_as_that_of_many_short_ones():
     assert narrow < 1.6 * wide
 
 
+@pytest.mark.parametrize("K", [4096, 4224, 8192, 8320, 16384, 16512, 32768, 32896, 131072])
+@pytest.mark.parametrize("act_group", [None, 128])
+@pytest.mark.parametrize("M", [1, 3])
+def test_activation_quantizer_on_both_sides_of_every_block_width(M, K, act_group):
+    # rows of up to 4096, 8192, 16384 and 32768 values are held in registers by 256, 512, 1024 and 1024 threads,
+    # longer ones read twice; the largest value of each row in its first, a middle and its last place
+    x = synth.make_x(M, K, seed=K + M)
+    for m, col in zip(range(M), (K - 1, 0, K // 2 - 1)):
+        x[m, col] = -1.5 * np.abs(x[m]).max()
+    xq_ref, xs_ref = ref.quantize_act(x, act_group)
+    xq, xs = mx.quantize_activations(dev(x), act_group)
+    assert np.array_equal(xs.cpu().numpy().view(np.uint16), xs_ref.view(np.uint16))
+    assert np.array_equal(xq.cpu().numpy(), xq_ref)
+
+
 @pytest.mark.parametrize("K", [512, 4096, 8192, 14336, 28672, 33024])
 @pytest.mark.parametrize("act_group", [None, 128])
 def test_a_nan_does_not_enter_the_scale_of_its_row(K, act_group):
