@@ -539,19 +539,21 @@ def test_fused_quantizer_and_linear_from_fp16(M, K, N, n8, variant):
 @pytest.mark.parametrize("K,groups", [(640, False), (640, True), (8192, False)])
 def test_tiled_stores_at_the_last_token_tile(path, rows, K, groups):
     # a last tile that is one row short, full, and one row over, of every block shape; K = 8192 with scratch,
-    # so that the parts of a K split go through the same stores; nothing is written past the last row
+    # so that the parts of a K split go through the same stores; nothing is written past the last row or part
     tile = int(path[len("prefill"):])
     M, N, n8 = tile + rows, 150, 21
     act_group = 128 if groups and path != "prefill128" else None
     _, _, L, x, xq, xs = make_case(M, K, N, n8, seed=tile + rows, w8_group=128 if groups else None, act_group=act_group)
     PL = pack_from_oracle(L)
-    need = mx.query_sizes(M, K, N, n8, act_group, L.w8_group)["linear_workspace_bytes"]
-    ws = torch.full((max(need, 4 * (1 << 20)) + 256,), 77, dtype=torch.uint8, device="cuda") if K >= 8192 else None
+    # scratch for exactly two parts of K (sums of every token and padded row), with guard bytes right behind it
+    need = 2 * M * (-(-n8 // 16) + -(-(N - n8) // 16)) * 16 * 4 if K >= 8192 else 0
+    ws = torch.full((need + 256,), 77, dtype=torch.uint8, device="cuda")
     buf = torch.full((M * N + 64,), -3.0, dtype=torch.float16, device="cuda")
-    y = mx.mixed_linear(dev(xq), dev(xs), PL, PATHS[path], out=buf[: M * N].view(M, N), workspace=None if ws is None else ws[:-256])
+    y = mx.mixed_linear(dev(xq), dev(xs), PL, PATHS[path], out=buf[: M * N].view(M, N), workspace=ws[:need] if need else None)
     check_against_oracle(y.cpu().numpy(), xq, xs, L, f"{path} M={M} K={K}")
     assert bool((buf[M * N:] == -3.0).all())
-    assert ws is None or bool((ws[-256:] == 77).all())
+    assert bool((ws[need:] == 77).all())
+    assert bool((ws[:need].view(torch.int32) != 0x4d4d4d4d).all())   # K was split, and both parts stored every sum
 
 
 def test_calls_go_to_the_current_stream():
