@@ -134,9 +134,8 @@ struct Shape {
 // of the wave and one column of `out` (rows of `stride` values).  Everything but the column and 4h is the same for the
 // whole wave, so the row address stays in scalar registers and the lane's part is one 32-bit offset: a value costs its
 // conversion, a scalar addition and the store.  (As (size_t)m * N + ch with a row check in front of each store, a value
-// took a 64-bit vector address, a comparison and two changes of the lane mask.  8B block: 79.9 -> 79.4 us at 48 tokens,
-// 138.7 -> 137.8 at 256, 543 -> 540 at 1024 with group-wise scales; 70B block at 777 tokens 1009.8 -> 1005.5.)
-// Only the last token tile of a ragged batch checks its rows.
+// took a 64-bit vector address, a comparison and two changes of the lane mask.)  Only the last token tile of a ragged
+// batch checks its rows.
 template <typename C, typename T, typename F>
 static __device__ inline void store_tile(T *out, int row0, int rows, int stride, int h, int column, bool valid, F &&f)
 {
@@ -397,8 +396,9 @@ static __device__ inline void prefill_block(const LinearParams &p, int m0, int t
     }
     const float sw_row = (PART8 && DUMP != 1 && !PG8) ? (float)p.s8[rw] : 0.0f;
     // Token scales of the epilogue (one per token): every thread fetches one and leaves it in LDS, where
-    // the epilogue finds the 16 TM a lane needs by 4 TM wide reads.  (Requested by each lane from
-    // memory, they were 16 TM two-byte loads per wave: 1.8 us of the 43 us a 128 x 128 block lives.)
+    // the epilogue finds the 16 TM a lane needs by 4 TM wide reads.  (Requested by each lane from memory,
+    // they were 16 TM two-byte loads per wave: a 128 x 128 block took 1.9 us from the end of its loop to its first
+    // store, now 0.5.)
     constexpr bool TOKEN_SCALES = ACT_PT && DUMP == 0;
     if constexpr (TOKEN_SCALES)
         if (tid < BM) lds_sa[tid] = (float)p.xscale[min(m0 + tid, p.M - 1)];
