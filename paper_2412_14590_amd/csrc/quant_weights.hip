@@ -227,10 +227,10 @@ static __device__ inline void quantize_tile8(const half_t *__restrict__ W, const
     }
 }
 
-// A block's 2^lr (at most 8) 8-bit rows, r0 and on, where there are too few tiles for the chip: lane = row + 2^lr * slot, a slot being 16
-// consecutive k, so that a load of a wave always holds whole groups of the rows it touches.  The waves take the
-// row's chunks (one load of a wave each) in turn, QP_AHEAD of them requested together.  With one scale per
-// channel the rows are walked twice (the second read comes from the L2 or the memory-side cache).
+// A block's 2^lr (at most 8) 8-bit rows, r0 and on, where there are too few tiles for the chip: lane = row +
+// 2^lr * slot, a slot being 16 consecutive k, so that a load of a wave always holds whole groups of the rows it
+// touches.  The waves take the row's chunks (one load of a wave each) in turn, QP_AHEAD of them requested together.
+// With one scale per channel the rows are walked twice (the second read comes from the L2 or the memory-side cache).
 constexpr int QP_AHEAD = 4;
 static __device__ inline void quantize_rows8(const half_t *__restrict__ W, const int32_t *__restrict__ perm, int K, int n8, int ng, int ngp,
                                              int w8_per_channel, int r0, int lr, int8_t *__restrict__ w8, half_t *__restrict__ s8,
