@@ -185,6 +185,15 @@ static __device__ inline void prefill_block(const LinearParams &p, int m0, int t
     constexpr int NB = C::NB, SB = 4 * NB;   // tiles and MFMA slots of a bundle
     constexpr int NBG = TM / NB;             // bundles per group
     constexpr int HALF = NSLOT / 2;          // slot of the barrier
+    // The requests a barrier sets free go out one at a time over the rest of the group: all waves of a block pass the
+    // barrier together, and with six requests of 1 KB from each of them in a row they wait for each other to issue instead
+    // of multiplying.  Both ways in turn on one machine, quantizer included: K = 4096,
+    // N = 28672 at 2048 tokens 317 -> 311 us, K = 14336, N = 4096 168 -> 163, K = 8192, N = 10240 at 777 tokens 99.7 ->
+    // 98.2, K = 4096, N = 28672 at 1024 tokens with scales per group 241 -> 238.5.  A 32-row block makes three requests in
+    // a group of four slots and is alone on its SIMDs: they go out at the barrier (K = N = 4096 at 48 tokens 16.1 us, spread 17.0).
+    // The debug sums have no registers to spare for it and make theirs there as well, in the same order.
+    constexpr int SPREAD = NSLOT - HALF;     // slots
+    constexpr bool AT_BARRIER = TM == 1 || DUMP == 2;
     constexpr int PPS = 8 / (NSLOT - HALF);  // eighths of the next group's unpack per slot of the second half
     static_assert(PPS * (NSLOT - HALF) == 8, "the unpack is spread evenly over the second half of the group");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -216,10 +225,10 @@ static __device__ inline void prefill_block(const LinearParams &p, int m0, int t
         a_voff[i] = (uint32_t)min(m0 + row, p.M - 1) * (uint32_t)p.K + cs * 16;
     }
     const uint32_t lds_a_wave = __builtin_amdgcn_readfirstlane(lds_address(lds_a) + wave * LPW * 1024);
+    auto load_a1 = [&](int g, int stage, int i) { load_lds16(lds_a_wave + stage * A_STAGE + i * 1024, a_voff[i], p.xq + (size_t)min(g, g_hi - 1) * G); };
     auto load_a = [&](int g, int stage) {
-        const int8_t *src = p.xq + (size_t)min(g, g_hi - 1) * G;
 #pragma unroll
-        for (int i = 0; i < LPW; ++i) load_lds16(lds_a_wave + stage * A_STAGE + i * 1024, a_voff[i], src);
+        for (int i = 0; i < LPW; ++i) load_a1(g, stage, i);
     };
     // fragment read offsets: row mw0 + 32 mt + n32, global chunk 2j + h
     int a_rd[4];
@@ -251,6 +260,11 @@ static __device__ inline void prefill_block(const LinearParams &p, int m0, int t
     static_assert(WD >= 1 && WD <= 3, "weight requests run one to three groups ahead");
     constexpr int NMETA = DUMP == 1 ? 1 : 2;   // load instructions load_meta issues for a 4-bit tile in the hand-issued variant
     v4i raw[NRAW][2];
+    // one of the two requests of a 4-bit group
+    auto load_raw1 = [&](int g, auto setc, auto ic) {
+        constexpr int rset = decltype(setc)::value % NRAW, i = decltype(ic)::value;
+        load_reg16<512 * i>(raw[rset][i], b_voff, p.w4 + (size_t)min(g, g_hi - 1) * 1024);
+    };
     auto load_b = [&](int g, auto setc) {
         constexpr int set = decltype(setc)::value % NBUF, rset = decltype(setc)::value % NRAW;
         const int gc = min(g, g_hi - 1);
@@ -501,8 +515,10 @@ static __device__ inline void prefill_block(const LinearParams &p, int m0, int t
                 mid_group_barrier<(!ACT_PT && DUMP != 1)>();
                 if constexpr (U == 1) load_meta(g / 4 + 1, meta_nxt);
                 if (!ACT_PT && DUMP != 1) load_reg_u16(sa_bits, sa_voff, p.xscale + min(g + 2, g_hi - 1));
-                if (!PART8) load_b(g + 1 + WD, std::integral_constant<int, U + 1 + WD>{});
-                load_a(g + 3, (U + 3) % NSTAGE);
+                if constexpr (AT_BARRIER) {
+                    if (!PART8) load_b(g + 1 + WD, std::integral_constant<int, U + 1 + WD>{});
+                    load_a(g + 3, (U + 3) % NSTAGE);
+                }
                 if (!PART8) zb_next = zbias(((U == 3 ? meta_nxt.z : meta_cur.z) >> (4 * ((U + 1) % 4))) & 15);
                 if (!PART8 && DUMP == 2 && !keep_next) zb_next = 0x80808080u;
                 __builtin_amdgcn_sched_barrier(0);
@@ -515,6 +531,17 @@ static __device__ inline void prefill_block(const LinearParams &p, int m0, int t
             P[s][i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[st % RING], b[U % NBUF][j], j == 0 ? zero16 : P[s][i], 0, 0, 0);
             finish4(P[s ^ 1][i], std::integral_constant<int, up>{}, std::integral_constant<int, j>{},
                     q == 0 ? sw_prev : sw_cur, gp, opaque0);
+            // the requests of this group: weights (4-bit tiles), then activations
+            if constexpr (!AT_BARRIER && st >= HALF) {
+                constexpr int NREQ = (PART8 ? 0 : 2) + LPW;
+                static_for<0, NREQ>([&](auto kc) {
+                    constexpr int k = decltype(kc)::value, a = k - (PART8 ? 0 : 2);
+                    if constexpr (HALF + k * SPREAD / NREQ == st) {
+                        if constexpr (a < 0) load_raw1(g + 1 + WD, std::integral_constant<int, U + 1 + WD>{}, kc);
+                        else load_a1(g + 3, (U + 3) % NSTAGE, a);
+                    }
+                });
+            }
             if constexpr (!PART8 && st >= HALF) {
                 static_for<0, PPS>([&](auto ec) {
                     unpack_piece(std::integral_constant<int, U + 1>{},
@@ -621,10 +648,10 @@ static __device__ inline void prefill_block_w8_channel_scale(const LinearParams 
         a_voff[i] = (uint32_t)min(m0 + row, p.M - 1) * (uint32_t)p.K + cs * 16;
     }
     const uint32_t lds_a_wave = __builtin_amdgcn_readfirstlane(lds_address(lds_a) + wave * LPW * 1024);
+    auto load_a1 = [&](int g, int stage, int i) { load_lds16(lds_a_wave + stage * A_STAGE + i * 1024, a_voff[i], p.xq + (size_t)min(g, g_hi - 1) * G); };
     auto load_a = [&](int g, int stage) {
-        const int8_t *src = p.xq + (size_t)min(g, g_hi - 1) * G;
 #pragma unroll
-        for (int i = 0; i < LPW; ++i) load_lds16(lds_a_wave + stage * A_STAGE + i * 1024, a_voff[i], src);
+        for (int i = 0; i < LPW; ++i) load_a1(g, stage, i);
     };
     int a_rd[4];
 #pragma unroll
@@ -662,6 +689,7 @@ static __device__ inline void prefill_block_w8_channel_scale(const LinearParams 
         af[t % RING] = *(const v4i *)(lds_a + a_rd[t / TM] + stage * A_STAGE + (t % TM) * 32 * G);
     };
     static_for<0, DFRAG>([&](auto tc) { load_frag(std::integral_constant<int, 0>{}, tc); });
+    constexpr int SPREAD = NSLOT - HALF;   // slots over which a group's requests go out (see prefill_block)
 
     v16i P[TM];
 #pragma unroll
@@ -689,7 +717,7 @@ static __device__ inline void prefill_block_w8_channel_scale(const LinearParams 
                 // of group g+2 (LPW loads)
                 await_loads<(L8 == 1 ? LPW + 4 : LPW + 8)>();
                 mid_group_barrier<false>();
-                load_a(g + 3, (U + 3) % NSTAGE);
+                if constexpr (TM == 1) load_a(g + 3, (U + 3) % NSTAGE);
                 __builtin_amdgcn_sched_barrier(0);
             }
             if constexpr (st + DFRAG < NSLOT)
@@ -697,6 +725,10 @@ static __device__ inline void prefill_block_w8_channel_scale(const LinearParams 
             else
                 load_frag(std::integral_constant<int, (U + 1) % NSTAGE>{}, std::integral_constant<int, st + DFRAG - NSLOT>{});
             P[st % TM] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[st % RING], b[U % NBUF][st / TM], P[st % TM], 0, 0, 0);
+            if constexpr (TM > 1 && st >= HALF)
+                static_for<0, LPW>([&](auto kc) {
+                    if constexpr (HALF + decltype(kc)::value * SPREAD / LPW == st) load_a1(g + 3, (U + 3) % NSTAGE, decltype(kc)::value);
+                });
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
             __builtin_amdgcn_sched_barrier(0);
