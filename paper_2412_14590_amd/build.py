@@ -33,7 +33,7 @@ def _hipcc():
 
 
 # sources with hand-issued loads -> the kernels in them that must not spill
-NO_SPILL = {"linear_prefill.hip": lambda n: "linear_prefill_kernel" in n,
+NO_SPILL = {"linear_prefill.hip": lambda n: "linear_prefill_kernel" in n or "linear_slices_kernel" in n,
             "linear_decode_split.hip": lambda n: "linear_decode_split_kernel" in n,
             "linear_mid.hip": lambda n: "linear_mid_kernel" in n}
 

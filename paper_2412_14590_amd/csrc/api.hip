@@ -151,6 +151,9 @@ namespace {
 
 int hip_status(int e) { return e == (int)hipSuccess ? MIXLLM_OK : MIXLLM_EHIP; }
 
+// the tiles cut along K over the waves of a block: taken by the library's choice only
+constexpr int PATH_SLICES = 100;
+
 // The library's choice of kernel.  Up to 16 tokens the decode path.  17 to 64 tokens lie between the
 // two paths the workload names.  Measured with every launch reading its weights from HBM (copies of
 // the layer rotating over 512 MB, as in a step of a model), on the Llama-shaped layers:
@@ -166,6 +169,7 @@ int hip_status(int e) { return e == (int)hipSuccess ? MIXLLM_OK : MIXLLM_EHIP; }
 int auto_path(const mixllm_desc &d, const LinearParams &p)
 {
     if (d.M <= 16) return MIXLLM_PATH_DECODE;
+    if (slices_pay(p)) return PATH_SLICES;
     if (d.M > 64 || !mid_covers(p)) return MIXLLM_PATH_PREFILL;
     const bool split = prefill_would_split(p);
     const long tiles = (long)(p.ntiles8 * TILE_N + 127) / 128 + (p.ntiles4 * TILE_N + 127) / 128;
@@ -194,6 +198,8 @@ int resolve_path(const mixllm_desc &d, const LinearParams &p, int path, LinearPa
         q.variant = path == MIXLLM_PATH_DECODE_STREAM ? DECODE_STREAM : path == MIXLLM_PATH_DECODE_RESIDENT ? DECODE_RESIDENT : DECODE_SPLIT;
         if (path == MIXLLM_PATH_DECODE_SPLIT && !decode_split_covers(q)) return MIXLLM_EUNSUPPORTED;
         return path;
+    case PATH_SLICES:
+        return path;
     case MIXLLM_PATH_MID:
         return (!mid_covers(p) || sums) ? MIXLLM_EUNSUPPORTED : path;
     case MIXLLM_PATH_PREFILL:
@@ -211,6 +217,7 @@ int run_path(const LinearParams &q, int path, hipStream_t st)
 {
     switch (path) {
     case MIXLLM_PATH_GENERIC: return hip_status(launch_linear_generic(q, st));
+    case PATH_SLICES: return hip_status(launch_linear_slices(q, st));
     case MIXLLM_PATH_MID: return hip_status(launch_linear_mid(q, st));
     case MIXLLM_PATH_PREFILL: return hip_status(launch_linear_prefill(q, st));
     default: return hip_status(launch_linear_decode(q, st));   // MIXLLM_PATH_DECODE and its variants

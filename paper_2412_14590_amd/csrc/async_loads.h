@@ -70,10 +70,14 @@ static __device__ inline void await_loads(uint2 &a, uint32_t &b)
 // Block-wide barrier in the middle of a group, written out instead of __syncthreads(): the
 // fence of the latter would wait for every outstanding load and LDS read.  The caller has
 // already waited for what must have landed; LDS_WRITES adds this wave's own LDS stores.
-template <bool LDS_WRITES>
+// BARRIER = false: a wave that shares its tile with no other waits for its own stores only.
+template <bool LDS_WRITES, bool BARRIER = true>
 static __device__ inline void mid_group_barrier()
 {
-    if (LDS_WRITES)
+    if (!BARRIER) {
+        if (LDS_WRITES) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        else asm volatile("" ::: "memory");
+    } else if (LDS_WRITES)
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     else
         asm volatile("s_barrier" ::: "memory");

@@ -229,6 +229,9 @@ int cu_count();
 bool decode_can_fuse_quantizer(const LinearParams &p);
 int launch_linear_prefill(const LinearParams &p, hipStream_t st);
 bool prefill_covers(const LinearParams &p);
+// tiles cut along K over the waves of a block (linear_prefill.hip): where they pay, and the launch
+bool slices_pay(const LinearParams &p);
+int launch_linear_slices(const LinearParams &p, hipStream_t st);
 // scratch bytes the tiled kernel would like for `p` (0 where it does not split K)
 size_t prefill_scratch_bytes(const LinearParams &p);
 // true when the tiled kernel, given p.partials / p.partials_cap, would split K for `p`

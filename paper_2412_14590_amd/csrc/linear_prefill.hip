@@ -97,7 +97,7 @@ __device__ unsigned long long *g_stamps;
 
 // compile-time loop: f(std::integral_constant<int, I>) for I in [I, N)
 template <int I, int N, typename F>
-static __device__ inline void static_for(F &&f)
+static __device__ __forceinline__ void static_for(F &&f)
 {
     if constexpr (I < N) {
         f(std::integral_constant<int, I>{});
@@ -109,6 +109,7 @@ template <int WM_, int WN_, int TM_, int WD_>
 struct Shape {
     static constexpr int WM = WM_, WN = WN_, TM = TM_;
     static constexpr int NW = WM * WN;
+    static constexpr bool ALONE = NW == 1;        // a wave with an activation tile of its own (linear_slices_kernel): nothing is shared, so the K loop has no barrier
     static constexpr int THREADS = 64 * NW;
     static constexpr int BM = WM * TM * 32;       // tokens per block
     static constexpr int BN = WN * 32;            // channels per block
@@ -164,6 +165,33 @@ static __device__ inline void store_tile(T *out, int row0, int rows, int stride,
     else go(std::false_type{});
 }
 
+// K slices of one output tile meet in LDS (linear_slices_kernel): every wave of the block leaves its sums in the place
+// of the activation stages, then each of them adds up some of the quads (four rows, one column a lane) in the order of
+// the slices and stores them.  value(mt, r): this wave's sum, T = float, or int32 where the sums are integers;
+// result(sum, m): what is stored for token m, the row given as its offset in the tile.
+template <typename C, typename T, typename V, typename R>
+static __device__ __forceinline__ void combine_slices(const LinearParams &p, int m0, int ch, uint8_t *smem, V &&value, R &&result)
+{
+    typedef T v4t __attribute__((ext_vector_type(4)));
+    constexpr int QUADS = C::TM * 4;
+    const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6, slices = blockDim.x >> 6, h = lane >> 5;
+    __syncthreads();   // nobody reads a stage any more, and nothing is on its way into one
+    v4t *cells = (v4t *)smem;   // [slice][quad][lane]
+    static_for<0, QUADS>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        cells[(slice * QUADS + q) * 64 + lane] = v4t{value(q / 4, 4 * (q % 4)), value(q / 4, 4 * (q % 4) + 1), value(q / 4, 4 * (q % 4) + 2), value(q / 4, 4 * (q % 4) + 3)};
+    });
+    __syncthreads();
+    for (int q = slice; q < QUADS; q += slices) {
+        v4t v = cells[q * 64 + lane];
+        for (int s = 1; s < slices; ++s) v += cells[(s * QUADS + q) * 64 + lane];
+        const int row = (q >> 2) * 32 + 8 * (q & 3) + 4 * h;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (m0 + row + i < p.M && ch >= 0) p.y[(size_t)(m0 + row + i) * p.N + ch] = result(v[i], row + i);
+    }
+}
+
 // ASYNC: packed weights and metadata are fetched with the hand-issued loads above.  Only valid in a
 // kernel that keeps everything in registers: a register spilled between its load and its
 // await_loads() would be saved before the data has arrived.  (The build checks that the kernels
@@ -175,8 +203,8 @@ static __device__ inline void store_tile(T *out, int row0, int rows, int stride,
 // entry point, the partials are added up in int32 over the groups instead of being rescaled:
 // same arguments, loads, waits, unpack and MFMAs as the linear.
 template <typename C, int DUMP, bool ACT_PT, bool PART8, bool PG8, bool ASYNC>
-static __device__ inline void prefill_block(const LinearParams &p, int m0, int t16_0, int g_lo, int g_hi, int kp, uint8_t *lds_a,
-                                            float *lds_sa)
+static __device__ __forceinline__ void prefill_block(const LinearParams &p, int m0, int t16_0, int g_lo, int g_hi, int kp, uint8_t *lds_a,
+                                            float *lds_sa, uint8_t *smem)
 {
     // The block walks the quantization groups g_lo .. g_hi - 1 (all of K, or - K split over kparts
     // blocks - part kp of it; g_lo is a multiple of 4, and so is g_hi unless it is the last group).
@@ -196,7 +224,7 @@ static __device__ inline void prefill_block(const LinearParams &p, int m0, int t
     constexpr bool AT_BARRIER = TM == 1 || DUMP == 2;
     constexpr int PPS = 8 / (NSLOT - HALF);  // eighths of the next group's unpack per slot of the second half
     static_assert(PPS * (NSLOT - HALF) == 8, "the unpack is spread evenly over the second half of the group");
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = C::ALONE ? threadIdx.x & 63 : threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = C::WM == 1 ? 0 : wave / WN, wn = wave % WN;
     const int n32 = lane & 31, h = lane >> 5;
     const int ntiles = PART8 ? p.ntiles8 : p.ntiles4;
@@ -512,7 +540,7 @@ static __device__ inline void prefill_block(const LinearParams &p, int m0, int t
                     const float sa_val = half_bits_to_float(sa_bits);
                     asm volatile("ds_write_b32 %0, %1" ::"v"(lds_sa_thread + (uint32_t)(((U + 1) % NSTAGE) * BM * sizeof(float))), "v"(sa_val) : "memory");
                 }
-                mid_group_barrier<(!ACT_PT && DUMP != 1)>();
+                mid_group_barrier<(!ACT_PT && DUMP != 1), !C::ALONE>();
                 if constexpr (U == 1) load_meta(g / 4 + 1, meta_nxt);
                 if (!ACT_PT && DUMP != 1) load_reg_u16(sa_bits, sa_voff, p.xscale + min(g + 2, g_hi - 1));
                 if constexpr (AT_BARRIER) {
@@ -582,6 +610,11 @@ static __device__ inline void prefill_block(const LinearParams &p, int m0, int t
     await_loads<0>(meta_nxt.s, meta_nxt.z);
     await_loads<0>(sa_bits);
     MIXLLM_STAMP(3);
+    if constexpr (C::ALONE) {
+        combine_slices<C, float>(p, m0, ch, smem, [&](int mt, int r) { return acc[mt][r]; },
+                                 [&](float v, int row) { return (half_t)(ACT_PT ? v * lds_sa[row] : v); });
+        return;
+    }
     if (DUMP == 1) return;
     if (DUMP == 2) {
         // (the channel passes through an empty asm statement so that no store address is computed,
@@ -626,12 +659,12 @@ static __device__ inline void prefill_block(const LinearParams &p, int m0, int t
 // scaled once at the end.  Same activation pipeline as prefill_block; the four token tiles are
 // four independent accumulation chains issued round robin.
 template <typename C, bool ACT_PT, int DUMP>
-static __device__ inline void prefill_block_w8_channel_scale(const LinearParams &p, int m0, int t16_0, int g_lo, int g_hi, int kp,
-                                                            uint8_t *lds_a, float *lds_sa)
+static __device__ __forceinline__ void prefill_block_w8_channel_scale(const LinearParams &p, int m0, int t16_0, int g_lo, int g_hi, int kp,
+                                                            uint8_t *lds_a, float *lds_sa, uint8_t *smem)
 {
     constexpr int TM = C::TM, WN = C::WN, BM = C::BM, A_STAGE = C::A_STAGE, LPW = C::LPW, DFRAG = C::DFRAG, RING = C::RING;
     constexpr int NSLOT = TM * 4, HALF = NSLOT / 2;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = C::ALONE ? threadIdx.x & 63 : threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     const int n32 = lane & 31, h = lane >> 5;
     const int mw0 = wm * TM * 32;
@@ -716,7 +749,7 @@ static __device__ inline void prefill_block_w8_channel_scale(const LinearParams 
                 // of the two has been waited for at the start of this group) and the activations
                 // of group g+2 (LPW loads)
                 await_loads<(L8 == 1 ? LPW + 4 : LPW + 8)>();
-                mid_group_barrier<false>();
+                mid_group_barrier<false, !C::ALONE>();
                 if constexpr (TM == 1) load_a(g + 3, (U + 3) % NSTAGE);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -743,6 +776,11 @@ static __device__ inline void prefill_block_w8_channel_scale(const LinearParams 
     // drain (see prefill_block): nothing in flight towards this block's LDS or registers
     static_for<0, NBUF>([&](auto sc) { await_loads<0>(b[decltype(sc)::value][0], b[decltype(sc)::value][1], b[decltype(sc)::value][2], b[decltype(sc)::value][3]); });
 
+    if constexpr (C::ALONE) {
+        combine_slices<C, int>(p, m0, ch, smem, [&](int mt, int r) { return P[mt][r]; },
+                               [&](int v, int row) { return (half_t)((float)v * sw_row * lds_sa[row]); });
+        return;
+    }
     if constexpr (DUMP == 2) {
 #pragma unroll
         for (int mt = 0; mt < TM; ++mt)
@@ -810,9 +848,9 @@ __global__ __launch_bounds__(C::THREADS, MINW) void linear_prefill_kernel(Linear
     auto tile8 = [&](auto shape) {
         using S = decltype(shape);
         if constexpr (W8PC && ACT_PT && DUMP != 1)
-            prefill_block_w8_channel_scale<S, ACT_PT, DUMP>(p, bm * S::BM, bn * T16, g_lo, g_hi, kp, lds_a, lds_sa);
+            prefill_block_w8_channel_scale<S, ACT_PT, DUMP>(p, bm * S::BM, bn * T16, g_lo, g_hi, kp, lds_a, lds_sa, smem);
         else
-            prefill_block<S, DUMP, ACT_PT, true, !W8PC, ASYNC>(p, bm * S::BM, bn * T16, g_lo, g_hi, kp, lds_a, lds_sa);
+            prefill_block<S, DUMP, ACT_PT, true, !W8PC, ASYNC>(p, bm * S::BM, bn * T16, g_lo, g_hi, kp, lds_a, lds_sa, smem);
     };
     if (part8) {
         // (8-bit tiles of 128 rows with a weight scale per group are not built: they do not fit the
@@ -823,12 +861,52 @@ __global__ __launch_bounds__(C::THREADS, MINW) void linear_prefill_kernel(Linear
         } else
             tile8(C8{});
     } else
-        prefill_block<C, DUMP, ACT_PT, false, false, ASYNC>(p, bm * C::BM, bn * T16, g_lo, g_hi, kp, lds_a, lds_sa);
+        prefill_block<C, DUMP, ACT_PT, false, false, ASYNC>(p, bm * C::BM, bn * T16, g_lo, g_hi, kp, lds_a, lds_sa, smem);
 #ifdef MIXLLM_STAMPS
     MIXLLM_STAMP(4);                                   // stores issued
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // ... and acknowledged
     MIXLLM_STAMP(5);
 #endif
+}
+
+// Grids of up to two tiles of 32 x 32 per CU.  There the tiled kernel is a race of serial chains: K = N = 4096 at 48 tokens
+// is 72 blocks of 32 x 128 on 256 CUs, each of them 32 groups of 0.3 us with one wave on a SIMD.  Here a block is one
+// tile of 32 tokens x 32 channels and its four waves take a quarter of K each (whole groups of 4 quantization groups),
+// with an activation tile of its own in LDS, the pipeline of prefill_block and no barrier in it; the quarters' sums meet
+// in LDS in a fixed order.  A quarter of the chain on four times the CUs, for four times the activation traffic, which
+// comes from the L2s: that traffic is what a step of four groups (24 KB a CU) then waits for, 0.5 us.  Measured from a
+// graph, weights from HBM, against the kernel that took the shape before: K = N = 4096 at 20 / 48 / 96 / 128 tokens
+// 10.8 / 13.6 / 13.8 / 13.7 -> 7.7 / 8.5 / 11.1 / 12.5 us; N = 6144 at 32 / 64 tokens 11.1 / 14.1 -> 8.4 / 11.5; K = N =
+// 8192 at 64 tokens 25.2 -> 21.7; K = 4096, N = 1024 at 300 tokens 12.1 -> 8.3.  Eight waves a block (two to a SIMD): 12.1
+// where four take 8.4; tiles of 64 tokens: 9.9.
+constexpr int SLICES = 4;
+constexpr size_t slices_lds_bytes(bool act_pt)
+{
+    return (size_t)SLICES * (NSTAGE * 32 * G + (act_pt ? 1 : NSTAGE) * 32 * sizeof(float));   // two blocks fit a CU
+}
+template <bool ACT_PT, bool W8PC>
+__global__ __launch_bounds__(64 * SLICES, 2) void linear_slices_kernel(LinearParams p, int nbm, int nb8, int nb4, int per4, int per8)
+{
+    using C = Shape<1, 1, 1, MIXLLM_PREFILL_WD_SMALL>;
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+    // (every XCD a contiguous range of the 4-bit tiles, then of the 8-bit ones, the token tiles of a column next to each other)
+    const int xcd = blockIdx.x & 7, i = blockIdx.x >> 3;
+    const bool part8 = i >= per4;
+    const int nb = part8 ? nb8 : nb4, L = part8 ? xcd * per8 + (i - per4) : xcd * per4 + i;
+    if (L >= nbm * nb) return;
+    const int bn = L / nbm, bm = L - bn * nbm;
+    const int slice = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int quads = (p.ng + 3) / 4;
+    const int g_lo = slice * quads / SLICES * 4, g_hi = min(p.ng, (slice + 1) * quads / SLICES * 4);   // (never empty: quads >= SLICES)
+    uint8_t *lds_a = smem + slice * NSTAGE * C::A_STAGE;
+    float *lds_sa = (float *)(smem + SLICES * NSTAGE * C::A_STAGE) + slice * (ACT_PT ? 1 : NSTAGE) * C::BM;
+    if (part8) {
+        if constexpr (W8PC && ACT_PT)
+            prefill_block_w8_channel_scale<C, ACT_PT, 0>(p, bm * C::BM, bn * 2, g_lo, g_hi, 0, lds_a, lds_sa, smem);
+        else
+            prefill_block<C, 0, ACT_PT, true, !W8PC, true>(p, bm * C::BM, bn * 2, g_lo, g_hi, 0, lds_a, lds_sa, smem);
+    } else
+        prefill_block<C, 0, ACT_PT, false, false, true>(p, bm * C::BM, bn * 2, g_lo, g_hi, 0, lds_a, lds_sa, smem);
 }
 
 // K split over several blocks: the parts' fp32 sums (workspace, [part][token][padded concatenated
@@ -1101,6 +1179,37 @@ int launch_linear_prefill(const LinearParams &p0, hipStream_t st)
     case 2: return launch_shape<Shape<1, 4, 2, MIXLLM_PREFILL_WD_SMALL>, 2>(p, st);
     default: return launch_shape<Shape<1, MIXLLM_PREFILL_WN_LARGE, 4, MIXLLM_PREFILL_WD_LARGE>, 2>(p, st);
     }
+}
+
+// Where linear_slices_kernel takes over.  It needs a group of 4 quantization groups for each of its waves, and pays while
+// all its blocks run at once, two to a CU (K = N = 4096 at 128 tokens, 520 blocks: 12.5 us against 13.7; N = 6144 at 96, 582
+// blocks: 14.7 against 14.0; at 128, 776 blocks: 15.6 against 14.1).  A long K is a long chain again: with two blocks on a
+// CU the line lies at K = 8192 (64 tokens, N = 8192: 21.7 against 25.2; K = 14336, N = 4096 at 100 tokens 30 against 24.7, K
+// split over blocks), with one at K = 14336 (N = 4096 at 20 tokens 17.8 against 19.4; N = 1000 at 130 13.4 against 17.8;
+// K = 28672, N = 2000 at 60 tokens 31 against 27).  Up to 16 tokens the decode kernels are ahead (K = N = 4096: 7.2 against
+// 7.8).  Beyond 64 tokens a call that brings the scratch to split K over blocks gets that split, and with it the same sums
+// as from the tiled path by name.
+bool slices_pay(const LinearParams &p)
+{
+    if (p.P || p.S || p.M <= 16 || p.ng < 4 * SLICES - 3 || !prefill_covers(p)) return false;
+    if (p.M > 64 && prefill_would_split(p)) return false;
+    const long blocks = (long)((p.M + 31) / 32) * ((p.ntiles8 + 1) / 2 + (p.ntiles4 + 1) / 2), cus = cu_count();
+    return blocks <= cus ? p.ng <= 112 : blocks <= 2 * cus + cus / 16 && p.ng <= 64;
+}
+
+int launch_linear_slices(const LinearParams &p, hipStream_t st)
+{
+    if (p.M == 0 || p.N == 0) return hipSuccess;
+    const int nbm = (p.M + 31) / 32, nb8 = (p.ntiles8 + 1) / 2, nb4 = (p.ntiles4 + 1) / 2;
+    const int per4 = (nbm * nb4 + 7) / 8, per8 = (nbm * nb8 + 7) / 8;
+    auto go = [&](auto kernel, bool act_pt) {
+        const size_t lds = slices_lds_bytes(act_pt);
+        if (int e = ensure_dynamic_lds((const void *)kernel, lds)) return e;
+        hipLaunchKernelGGL(kernel, dim3((per4 + per8) * 8), dim3(64 * SLICES), lds, st, p, nbm, nb8, nb4, per4, per8);
+        return (int)hipGetLastError();
+    };
+    if (p.act_per_token) return p.w8_per_channel ? go(linear_slices_kernel<true, true>, true) : go(linear_slices_kernel<true, false>, true);
+    return p.w8_per_channel ? go(linear_slices_kernel<false, true>, false) : go(linear_slices_kernel<false, false>, false);
 }
 
 // the launch plan as thirteen integers (token rows and channels of a block tile of the 4-bit part, its

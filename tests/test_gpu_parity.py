@@ -461,6 +461,26 @@ def test_tiled_path_with_k_split_over_blocks(M, K, N, n8, variant):
     check_against_oracle(yf.cpu().numpy(), xq, xs, L, ("fp16 entry", variant, M, K, N, n8))
 
 
+@pytest.mark.parametrize("variant", ["baseline", "paper", "w8_grouped"])
+@pytest.mark.parametrize("M,K,N,n8", [
+    (17, 1664, 16, 3), (32, 1664, 33, 33), (33, 1920, 70, 0), (65, 4224, 64, 6),      # 4 quads (one of 1 and of 3 groups), 9: uneven shares
+    (17, 14336, 300, 30), (300, 4096, 257, 26), (64, 8192, 1000, 100),                # the longest K it takes; many token tiles
+    (40, 1920, 4095, 409), (32, 2048, 8192, 31), (48, 2048, 8448, 0), (48, 2048, 8449, 0)])   # around one and two blocks a CU
+def test_tiles_cut_along_k_over_the_waves_of_a_block(M, K, N, n8, variant):
+    # Small grids (the library's choice, no path of its own): four waves of a block take a quarter of K each and add
+    # their sums up in LDS.  Against the oracle by row norm and per element, bit-identical between runs and between the
+    # entry points, nothing written outside y.
+    ag, wg = {"baseline": (None, None), "paper": (128, 128), "w8_grouped": (None, 128)}[variant]
+    _, _, L, x, xq, xs = make_case(M, K, N, n8, seed=37, w8_group=wg, act_group=ag)
+    PL = pack_from_oracle(L)
+    buf = torch.full((M * N + 64,), -3.0, dtype=torch.float16, device="cuda")
+    y = mx.mixed_linear(dev(xq), dev(xs), PL, out=buf[: M * N].view(M, N))
+    check_against_oracle(y.cpu().numpy(), xq, xs, L, ("slices", variant, M, K, N, n8))
+    assert bool((buf[M * N:] == -3.0).all())
+    assert torch.equal(y, mx.mixed_linear(dev(xq), dev(xs), PL))
+    assert torch.equal(y, mx.linear_fp16(dev(x), PL, act_group=ag))
+
+
 @pytest.mark.parametrize("M,K,N,n8", [(17, 256, 7, 2), (33, 384, 70, 70), (64, 1024, 530, 0), (50, 640, 50, 5),
                                      (64, 512, 300, 30), (20, 4096, 1000, 100), (64, 14336, 272, 27), (1, 512, 96, 9),
                                      (48, 2048, 2070, 207)])
