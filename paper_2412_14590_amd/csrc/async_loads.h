@@ -38,6 +38,10 @@ static __device__ inline void load_reg8(uint2 &dst, uint32_t voff, const void *s
 {
     asm volatile("global_load_dwordx2 %0, %1, %2" : "=&v"(dst) : "v"(voff), "s"(sbase) : "memory");
 }
+static __device__ inline void load_reg4(uint32_t &dst, uint32_t voff, const void *sbase)
+{
+    asm volatile("global_load_dword %0, %1, %2" : "=&v"(dst) : "v"(voff), "s"(sbase) : "memory");
+}
 static __device__ inline void load_reg_u16(uint32_t &dst, uint32_t voff, const void *sbase)
 {
     asm volatile("global_load_ushort %0, %1, %2" : "=&v"(dst) : "v"(voff), "s"(sbase) : "memory");

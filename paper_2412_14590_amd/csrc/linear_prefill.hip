@@ -238,7 +238,9 @@ static __device__ __forceinline__ void prefill_block(const LinearParams &p, int 
     const int t16 = t16_0 + wn * 2 + (n32 >> 4);
     const int tile16 = min(t16, ntiles - 1);
     const int rw = tile16 * TILE_N + (n32 & 15);
-    const int ch = (t16 < ntiles && rw < nrows) ? p.perm[joff + rw] : -1;
+    const bool has_channel = t16 < ntiles && rw < nrows;
+    int ch = -1;   // ... in the output: fetched in the prologue (by the debug variants here)
+    if constexpr (DUMP != 0) ch = has_channel ? p.perm[joff + rw] : -1;
 
     // ---- loaders -------------------------------------------------------------------
     // Activation tile of one group, straight to LDS.  Load i of this wave fills rows
@@ -415,43 +417,56 @@ static __device__ __forceinline__ void prefill_block(const LinearParams &p, int 
     };
 
     // ---- prologue ------------------------------------------------------------------
+    // The requests in the order the K loop makes them (behind what is fetched once), as its counts expect to find them;
+    // it starts when its first group's have landed.  (Waiting for all three groups' cost a lone block half a microsecond.)
     Meta meta_cur, meta_nxt;
+    // (All of them by hand: a load of the compiler's that is in flight when the loop starts has it wait for everything
+    // inside the loop.)
+    uint32_t sa_bits = 0, sa_first = 0, ts_bits = 0, sw_bits = 0, ch_bits = 0;
+    if constexpr (DUMP == 0) load_reg4(ch_bits, (uint32_t)(joff + min(rw, nrows - 1)) * 4u, p.perm);
     load_meta(g_lo / 4, meta_cur);
-    load_b(g_lo, std::integral_constant<int, 0>{});
-    if (!PART8) static_for<1, WD + 1>([&](auto gc) { load_b(g_lo + decltype(gc)::value, gc); });
-    else static_for<1, L8>([&](auto gc) { load_b(g_lo + decltype(gc)::value, gc); });
-    load_a(g_lo, 0);
-    load_a(g_lo + 1, 1);
-    load_a(g_lo + 2, 2);
     // Activation scale (fp16 bits) of (token row tid, group g+1) on its way to LDS: every thread
     // requests one (rows past the tile re-read its last row), so that all waves count the same loads.
-    uint32_t sa_bits = 0;
     const uint32_t sa_voff = (uint32_t)min(m0 + min(tid, BM - 1), p.M - 1) * (uint32_t)ng * 2u;
     const uint32_t lds_sa_thread = lds_address(lds_sa) + (uint32_t)min(tid, BM - 1) * (uint32_t)sizeof(float);   // this thread's cell of stage 0
     if (!ACT_PT && DUMP != 1) {
-        if (tid < BM) {
-#pragma unroll
-            for (int s = 1; s < NSTAGE; ++s) lds_sa[s * BM + tid] = 0.0f;   // read (times a zero scale) before first written
-            lds_sa[tid] = (float)p.xscale[(size_t)min(m0 + tid, p.M - 1) * ng + g_lo];
-        }
+        load_reg_u16(sa_first, sa_voff, p.xscale + g_lo);
         load_reg_u16(sa_bits, sa_voff, p.xscale + min(g_lo + 1, g_hi - 1));
     }
-    const float sw_row = (PART8 && DUMP != 1 && !PG8) ? (float)p.s8[rw] : 0.0f;
     // Token scales of the epilogue (one per token): every thread fetches one and leaves it in LDS, where
     // the epilogue finds the 16 TM a lane needs by 4 TM wide reads.  (Requested by each lane from memory,
     // they were 16 TM two-byte loads per wave: a 128 x 128 block took 1.9 us from the end of its loop to its first
     // store, now 0.5.)
     constexpr bool TOKEN_SCALES = ACT_PT && DUMP == 0;
+    if constexpr (TOKEN_SCALES) load_reg_u16(ts_bits, (uint32_t)min(m0 + min(tid, BM - 1), p.M - 1) * 2u, p.xscale);
+    if constexpr (PART8 && DUMP != 1 && !PG8) load_reg_u16(sw_bits, (uint32_t)rw * 2u, p.s8);
+    static_for<0, 4>([&](auto vc) {
+        constexpr int v = decltype(vc)::value, w = PART8 ? v + L8 - 4 : v + WD - 3;
+        if constexpr (w >= 0) load_b(g_lo + w, std::integral_constant<int, w>{});
+        if constexpr (v >= 1) load_a(g_lo + v - 1, v - 1);
+    });
+    // younger than the first group's requests (an 8-bit tile of one group's look-ahead and the debug variants wait for all)
+    constexpr int YOUNGER0 = DUMP != 0 ? 0 : PART8 ? (L8 == 3 ? 2 * (LPW + 4) : 0) : WD == 1 ? 2 * LPW + 2 : 2 * (LPW + 2);
+    await_loads<YOUNGER0>(meta_cur.s, meta_cur.z);
+    await_loads<YOUNGER0>(sa_bits);
+    await_loads<YOUNGER0>(sa_first);
+    await_loads<YOUNGER0>(ts_bits);
+    await_loads<YOUNGER0>(sw_bits);
+    if constexpr (DUMP == 0) {
+        await_loads<YOUNGER0>(ch_bits);
+        ch = has_channel ? (int)ch_bits : -1;
+    }
+    if constexpr (PART8) await_loads<YOUNGER0>(b[0][0], b[0][1], b[0][2], b[0][3]);
+    else await_loads<YOUNGER0>(raw[0][0], raw[0][1]);
+    const float sw_row = half_bits_to_float(sw_bits);
+    if (!ACT_PT && DUMP != 1 && tid < BM) {
+#pragma unroll
+        for (int s = 1; s < NSTAGE; ++s) lds_sa[s * BM + tid] = 0.0f;   // read (times a zero scale) before first written
+        lds_sa[tid] = half_bits_to_float(sa_first);
+    }
     if constexpr (TOKEN_SCALES)
-        if (tid < BM) lds_sa[tid] = (float)p.xscale[min(m0 + tid, p.M - 1)];
-    // everything above has landed (registers and LDS)
-    await_loads<0>(meta_cur.s, meta_cur.z);
-    await_loads<0>(sa_bits);
-    if constexpr (PART8)
-        static_for<0, L8>([&](auto sc) { await_loads<0>(b[decltype(sc)::value][0], b[decltype(sc)::value][1], b[decltype(sc)::value][2], b[decltype(sc)::value][3]); });
-    else
-        static_for<0, NRAW>([&](auto rc) { await_loads<0>(raw[decltype(rc)::value][0], raw[decltype(rc)::value][1]); });
-    __syncthreads();
+        if (tid < BM) lds_sa[tid] = half_bits_to_float(ts_bits);
+    mid_group_barrier<true>();
     MIXLLM_STAMP(1);
     meta_nxt = meta_cur;
     if (!PART8) {
@@ -671,7 +686,7 @@ static __device__ __forceinline__ void prefill_block_w8_channel_scale(const Line
     const int t16 = t16_0 + wn * 2 + (n32 >> 4);
     const int tile16 = min(t16, p.ntiles8 - 1);
     const int rw = tile16 * TILE_N + (n32 & 15);
-    const int ch = (t16 < p.ntiles8 && rw < p.n8) ? p.perm[rw] : -1;
+    const bool has_channel = t16 < p.ntiles8 && rw < p.n8;
 
     uint32_t a_voff[LPW];
 #pragma unroll
@@ -704,17 +719,27 @@ static __device__ __forceinline__ void prefill_block_w8_channel_scale(const Line
         load_reg16<1536>(b[set][3], b_voff, base);
     };
 
-    static_for<0, L8>([&](auto gc) { load_b(g_lo + decltype(gc)::value, gc); });
-    load_a(g_lo, 0);
-    load_a(g_lo + 1, 1);
-    load_a(g_lo + 2, 2);
     static_assert(ACT_PT, "an integer sum over groups needs an activation scale that does not depend on the group");
     static_assert(DUMP != 1, "one accumulator over all of K: there is no per-group partial to dump");
-    const float sw_row = (float)p.s8[rw];
-    // token scales of the epilogue (see prefill_block)
-    if (DUMP == 0 && tid < BM) lds_sa[tid] = (float)p.xscale[min(m0 + tid, p.M - 1)];
-    static_for<0, L8>([&](auto sc) { await_loads<0>(b[decltype(sc)::value][0], b[decltype(sc)::value][1], b[decltype(sc)::value][2], b[decltype(sc)::value][3]); });
-    __syncthreads();
+    // the prologue of prefill_block
+    uint32_t sw_bits = 0, ts_bits = 0, ch_bits;
+    load_reg4(ch_bits, (uint32_t)min(rw, p.n8 - 1) * 4u, p.perm);
+    load_reg_u16(sw_bits, (uint32_t)rw * 2u, p.s8);
+    if (DUMP == 0) load_reg_u16(ts_bits, (uint32_t)min(m0 + min(tid, BM - 1), p.M - 1) * 2u, p.xscale);   // token scales of the epilogue
+    static_for<0, 3>([&](auto vc) {
+        constexpr int v = decltype(vc)::value;
+        if constexpr (v < L8) load_b(g_lo + v, vc);
+        load_a(g_lo + v, v);
+    });
+    constexpr int YOUNGER0 = L8 == 3 ? 2 * (LPW + 4) : 0;
+    await_loads<YOUNGER0>(sw_bits);
+    await_loads<YOUNGER0>(ts_bits);
+    await_loads<YOUNGER0>(ch_bits);
+    const int ch = has_channel ? (int)ch_bits : -1;
+    await_loads<YOUNGER0>(b[0][0], b[0][1], b[0][2], b[0][3]);
+    const float sw_row = half_bits_to_float(sw_bits);
+    if (DUMP == 0 && tid < BM) lds_sa[tid] = half_bits_to_float(ts_bits);
+    mid_group_barrier<true>();
     v4i af[RING];
     // slot t: k step t / TM, token tile t % TM
     auto load_frag = [&](auto stagec, auto tc) {
