@@ -1,4 +1,5 @@
-"""ctypes binding of libmixllm_hip.so: argument marshalling only.
+"""Binding of libmixllm_hip.so: argument marshalling only - ctypes, and for the calls a model makes for every
+layer the native module _calls (csrc/pycalls.cpp).
 
 PyTorch supplies device memory (tensors) and the current HIP stream; every step of the
 quantized linear runs in the library's own kernels.  There is no fallback: if the shared
@@ -41,12 +42,13 @@ class _Sizes(C.Structure):
 
 
 _lib = None
+_native = None
 _VP = C.c_void_p
 
 
 def lib():
     """Load the shared library (built in-tree by paper_2412_14590_amd/build.py)."""
-    global _lib
+    global _lib, _native
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise MixllmError(f"{LIB_PATH} is missing: build it with `python -m paper_2412_14590_amd.build` "
@@ -82,8 +84,30 @@ def lib():
                      "mixllm_mixed_linear", "mixllm_mixed_linear_path", "mixllm_debug_group_partials",
                      "mixllm_mixed_linear_fp16", "mixllm_mixed_linear_fp16_static", "mixllm_debug_channel_sums"):
             getattr(L, name).restype = C.c_int
+        try:
+            from . import _calls
+        except ImportError as e:
+            raise MixllmError(f"{os.path.join(HERE, '_calls.so')} is missing or does not load ({e}): build it with "
+                              "`python -m paper_2412_14590_amd.build` (there is no fallback)") from e
+        _calls.bind(*(C.cast(f, _VP).value for f in (L.mixllm_query_sizes, L.mixllm_quantize_activations,
+                                                     L.mixllm_mixed_linear_path, L.mixllm_mixed_linear_fp16)))
+        _native = _calls
         _lib = L
     return _lib
+
+
+def _calls():
+    """The native module, bound to the loaded library."""
+    if _native is None:
+        lib()
+    return _native
+
+
+def _result(r, what: str):
+    """What a native call returned: its result, or a status as a number."""
+    if type(r) is int:
+        _check(r, what)
+    return r
 
 
 def _check(rc: int, what: str):
@@ -217,33 +241,15 @@ def unpack_weights(L: PackedLayer) -> dict:
 
 def quantize_activations(x: torch.Tensor, act_group=None, out=None):
     """fp16 x [M,K] -> (xq int8 [M,K], xscale fp16 [M, K/act_group])."""
-    assert x.dtype == torch.float16 and x.dim() == 2
-    M, K = x.shape
-    act_group = K if act_group is None else act_group
-    if out is None:
-        xq = x.new_empty((M, K), dtype=torch.int8)
-        xs = x.new_empty((M, K // act_group))
-    else:
-        xq, xs = out
-    d = _desc(M, K, 1, 0, act_group, None)
-    _check(lib().mixllm_quantize_activations(C.byref(d), _ptr(x), _ptr(xq), _ptr(xs), _stream()),
-           "mixllm_quantize_activations")
-    return xq, xs
+    xq, xs = (None, None) if out is None else out
+    return _result(_calls().quantize_activations(x, act_group, xq, xs, _stream()), "mixllm_quantize_activations")
 
 
 def mixed_linear(xq: torch.Tensor, xs: torch.Tensor, L: PackedLayer, path: int = PATH_AUTO, out=None, workspace=None):
     """The quantized linear: (xq, xscale, packed layer) -> y fp16 [M,N] in original channel order.
     `workspace` (optional uint8 tensor, query_sizes()['linear_workspace_bytes']) lets the tiled path split K."""
-    M, K = xq.shape
-    assert K == L.K and xs.shape[0] == M
-    act_group = K // xs.shape[1]
-    y = xq.new_empty((M, L.N), dtype=torch.float16) if out is None else out
-    d = L.desc(M, act_group)
-    wb = 0 if workspace is None else workspace.numel()
-    _check(lib().mixllm_mixed_linear_path(C.byref(d), _ptr(xq), _ptr(xs), _ptr(L.w4), _ptr(L.w8), _ptr(L.s4),
-                                          _ptr(L.s8), _ptr(L.z4), _ptr(L.perm), _ptr(y), _ptr(workspace), wb, path,
-                                          _stream()), "mixllm_mixed_linear")
-    return y
+    return _result(_calls().mixed_linear(xq, xs, L.K, L.N, L.n8, L.w8_group, L.w8, L.w4, L.s8, L.s4, L.z4, L.perm, path, out,
+                                         workspace, _stream()), "mixllm_mixed_linear")
 
 
 def debug_group_partials(xq: torch.Tensor, L: PackedLayer, path: int = PATH_AUTO) -> torch.Tensor:
@@ -280,23 +286,9 @@ def linear_fp16(x: torch.Tensor, L: PackedLayer, act_group=None, out=None, works
     where the decode kernel can quantize its own activations, otherwise quantizer + linear with
     xq / xscale in `workspace` (a uint8 tensor of query_sizes()['workspace_bytes'], allocated here
     when not given)."""
-    assert x.dtype == torch.float16 and x.dim() == 2
-    M, K = x.shape
-    assert K == L.K
-    d = L.desc(M, act_group)
-    y = x.new_empty((M, L.N)) if out is None else out
-    if workspace is None:
-        # asked with the descriptor at hand, one field read.  A token through the four linears of the 8B block
-        # is bound by the host (the kernels take 31.5 us): 51 us while this query, the stream's Python object and
-        # the allocations' keyword arguments were 4.4 of the 13 us of a call, 36 without them
-        s = _Sizes()
-        _check(lib().mixllm_query_sizes(C.byref(d), C.byref(s)), "mixllm_query_sizes")
-        workspace = x.new_empty(s.workspace_bytes, dtype=torch.uint8)
-    wb = workspace.numel()
-    _check(lib().mixllm_mixed_linear_fp16(C.byref(d), _ptr(x), _ptr(L.w4), _ptr(L.w8), _ptr(L.s4), _ptr(L.s8),
-                                          _ptr(L.z4), _ptr(L.perm), _ptr(y), _ptr(workspace), wb, _stream()),
-           "mixllm_mixed_linear_fp16")
-    return y
+    return _result(_calls().linear_fp16(x, L.K, L.N, L.n8, L.w8_group, L.w8, L.w4, L.s8, L.s4, L.z4, L.perm,
+                                        L.K if act_group is None else act_group, out, workspace, _stream()),
+                   "mixllm_mixed_linear_fp16")
 
 
 def linear_fp16_static(x: torch.Tensor, L: PackedLayer, out: torch.Tensor, act_group=None) -> torch.Tensor:

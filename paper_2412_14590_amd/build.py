@@ -14,6 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.environ.get("MIXLLM_LIB_OUT", os.path.join(HERE, "libmixllm_hip.so"))
 PROBE_LIB = os.path.join(HERE, "libmixllm_probe.so")
+CALLS = os.path.join(HERE, "_calls.so")   # the native part of the Python binding (binding.py)
 SOURCES = ["api.hip", "quant_act.hip", "quant_weights.hip", "linear_generic.hip",
            "linear_decode.hip", "linear_decode_split.hip", "linear_mid.hip", "linear_prefill.hip", "salience.hip"]
 
@@ -209,6 +210,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
     subprocess.run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], check=True)
     if variant:
         return LIB
+    build_calls()
     # the ceiling probes of the benchmark: a separate small library
     r = subprocess.run([_hipcc(), *FLAGS, "-shared", "-o", PROBE_LIB, os.path.join(CSRC, "probe.hip")],
                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
@@ -216,6 +218,24 @@ def build(force: bool = True, verbose: bool = False) -> str:
         print(r.stdout, file=sys.stderr)
         raise RuntimeError("hipcc failed on probe.hip")
     return LIB
+
+
+def build_calls() -> str:
+    """Compile csrc/pycalls.cpp against the installed torch: host code only."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    src = os.path.join(CSRC, "pycalls.cpp")
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", INCLUDE, "-isystem", sysconfig.get_paths()["include"],
+           *[a for p in cpp_extension.include_paths() for a in ("-isystem", p)], src, "-o", CALLS,
+           *[f"-L{p}" for p in cpp_extension.library_paths()], "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        print(r.stdout, file=sys.stderr)
+        raise RuntimeError("g++ failed on pycalls.cpp")
+    return CALLS
 
 
 def build_sanitized_host(driver_cpp: str, exe: str) -> str:

@@ -583,6 +583,37 @@ def test_calls_go_to_the_current_stream():
             assert binding._stream() == torch.cuda.current_stream().cuda_stream == s.cuda_stream
 
 
+def test_calls_from_python_check_their_arguments_and_return_the_callers_tensors():
+    _, _, L, x, xq, xs = make_case(5, 512, 64, 6, seed=41)
+    PL, x, xq, xs = pack_from_oracle(L), dev(x), dev(xq), dev(xs)
+    wide = torch.zeros((5, 1024), dtype=torch.float16, device="cuda")
+    for bad in (x.float(), x[0], wide, wide[:, ::2], x.cpu()):      # type, dimensions, columns, strides, device
+        with pytest.raises(AssertionError):
+            mx.linear_fp16(bad, PL)
+    for bad in (x.float(), x[0], wide[:, ::2], x.cpu()):
+        with pytest.raises(AssertionError):
+            mx.quantize_activations(bad)
+    for bad in ((xq[:, :256], xs), (xq[:3], xs), (xq, xs.cpu()), (wide.to(torch.int8)[:, ::2], xs)):
+        with pytest.raises(AssertionError):
+            mx.mixed_linear(*bad, PL)
+    for act_group in (64, 3):                                       # a group size the library does not have
+        with pytest.raises(mx.MixllmError) as e:
+            mx.linear_fp16(x, PL, act_group)
+        assert e.value.status == -2
+        with pytest.raises(mx.MixllmError):
+            mx.quantize_activations(x, act_group)
+    with pytest.raises(TypeError):
+        mx.linear_fp16([1.0], PL)
+    y, q, s = torch.empty((5, 64), dtype=torch.float16, device="cuda"), torch.empty_like(xq), torch.empty_like(xs)
+    assert mx.linear_fp16(x, PL, out=y) is y
+    qs = mx.quantize_activations(x, out=(q, s))
+    assert qs[0] is q and qs[1] is s and torch.equal(q, xq) and torch.equal(s, xs)
+    y2 = torch.empty_like(y)
+    assert mx.mixed_linear(q, s, PL, out=y2) is y2 and torch.equal(y, y2)
+    empty = mx.linear_fp16(x[:0], PL)
+    assert empty.shape == (0, 64) and empty.dtype == torch.float16
+
+
 def test_fused_entry_point_rejects_a_short_workspace():
     W, sal, L, x, xq, xs = make_case(40, 512, 64, 6, seed=32)
     PL = pack_from_oracle(L)
