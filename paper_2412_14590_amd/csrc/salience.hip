@@ -143,10 +143,23 @@ __device__ inline SelectRank pick_digit(SelectState *st, int pass, uint32_t *wav
     return out;
 }
 
-// clears the counters and starts the ranks; the layers' counts start at zero
-__global__ __launch_bounds__(256) void select_init_kernel(SelectState *st, uint32_t T, int32_t *layer_counts, int L)
+// The layer offsets come from a host array that may be gone when the call returns, and the call
+// must neither block nor stage a copy: they travel as kernel arguments, 128 at a time.
+struct OffsetChunk {
+    int64_t v[128];
+};
+__global__ void select_offsets_kernel(int64_t *dst, int n, OffsetChunk c)
+{
+    const int t = threadIdx.x;
+    if (t < n) dst[t] = c.v[t];
+}
+
+// clears the counters and starts the ranks; the layers' counts start at zero; the first `n` layer offsets (a launch of
+// their own in front of the first histogram cost a search over 32 layers 4 us)
+__global__ __launch_bounds__(256) void select_init_kernel(SelectState *st, uint32_t T, int32_t *layer_counts, int L, int64_t *offsets, int n, OffsetChunk c)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
+    if (blockIdx.x == 1 && (int)threadIdx.x < n) offsets[threadIdx.x] = c.v[threadIdx.x];
     if (i < SEL_PASSES * SEL_BINS) (&st->hist[0][0])[i] = 0;
     if (i == 0) st->rank[0] = SelectRank{0, T};
     for (int l = i; l < L; l += gridDim.x * 256) layer_counts[l] = 0;
@@ -161,14 +174,24 @@ __global__ __launch_bounds__(SEL_THREADS) void select_hist_kernel(const uint32_t
     __shared__ SelectRank found;
     h[threadIdx.x] = 0;
     h[threadIdx.x + SEL_THREADS] = 0;
+    // The first four keys of a thread (all it has on up to a million channels) are requested before the digit is picked:
+    // two trips to memory at a time instead of one after the other.
+    constexpr int FIRST = 4;
+    const int64_t i0 = (int64_t)blockIdx.x * SEL_THREADS + threadIdx.x, step = (int64_t)gridDim.x * SEL_THREADS;
+    uint32_t first[FIRST];
+#pragma unroll
+    for (int j = 0; j < FIRST; ++j) first[j] = keys[min(i0 + j * step, total - 1)];
     uint32_t prefix = 0;
     if constexpr (PASS > 0) prefix = pick_digit(st, PASS - 1, wave_tot, &found).prefix;
     __syncthreads();
     constexpr int above = PASS == 0 ? 31 : sel_shift(PASS > 0 ? PASS - 1 : 0);
-    for (int64_t i = (int64_t)blockIdx.x * SEL_THREADS + threadIdx.x; i < total; i += (int64_t)gridDim.x * SEL_THREADS) {
-        const uint32_t k = keys[i];
+    auto take = [&](uint32_t k) {
         if (PASS == 0 || (k >> above) == (prefix >> above)) atomicAdd(&h[(k >> sel_shift(PASS)) & sel_mask(PASS)], 1u);
-    }
+    };
+#pragma unroll
+    for (int j = 0; j < FIRST; ++j)
+        if (i0 + j * step < total) take(first[j]);
+    for (int64_t i = i0 + FIRST * step; i < total; i += step) take(keys[i]);
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
@@ -183,13 +206,15 @@ __global__ __launch_bounds__(SEL_THREADS) void select_count_kernel(const uint32_
     __shared__ uint32_t wave_tot[SEL_THREADS / 64];
     __shared__ SelectRank found;
     __shared__ uint32_t s_gt, s_eq;
+    const int64_t lo = (int64_t)blockIdx.x * tile, hi = min(lo + tile, total);
+    uint32_t next = keys[min(lo + (int64_t)threadIdx.x, total - 1)];   // (requested before the threshold is known)
     const uint32_t thr = pick_digit(st, SEL_PASSES - 1, wave_tot, &found).prefix;
     if (threadIdx.x == 0) s_gt = s_eq = 0;
     __syncthreads();
-    const int64_t lo = (int64_t)blockIdx.x * tile, hi = min(lo + tile, total);
     uint32_t a = 0, b = 0;
     for (int64_t i = lo + threadIdx.x; i < hi; i += SEL_THREADS) {
-        const uint32_t k = keys[i];
+        const uint32_t k = next;
+        next = keys[min(i + SEL_THREADS, total - 1)];
         a += k > thr;
         b += k == thr;
     }
@@ -221,6 +246,10 @@ __global__ __launch_bounds__(SEL_THREADS) void select_emit_kernel(const uint32_t
     const int tid = threadIdx.x, lane = tid & 63;
     // the search for a channel's layer is a chain of dependent reads: from LDS unless there are very many layers
     const bool in_lds = L < SEL_OFFSETS;
+    // everything the block starts from is requested at once
+    const int64_t lo = (int64_t)blockIdx.x * tile, hi = min(lo + tile, total);
+    uint32_t next = keys[min(lo + (int64_t)tid, total - 1)];
+    const uint32_t gt_before = tid < (int)blockIdx.x ? st->tile_gt[tid] : 0u, eq_before = tid < (int)blockIdx.x ? st->tile_eq[tid] : 0u;
     if (in_lds && tid <= L) s_off[tid] = offsets[tid];
     auto layer_of = [&](int64_t c) {   // the last layer that starts at or before c (an empty one starts where the next does)
         int l = 0, r = L;              // offset of l <= c < offset of r
@@ -233,13 +262,13 @@ __global__ __launch_bounds__(SEL_THREADS) void select_emit_kernel(const uint32_t
     };
     const uint32_t thr = st->rank[SEL_PASSES].prefix, take = st->rank[SEL_PASSES].remaining;
     uint32_t gt_seen, eq_seen;
-    block_exclusive_scan(tid < (int)blockIdx.x ? st->tile_gt[tid] : 0u, wave_tot, gt_seen);
-    block_exclusive_scan(tid < (int)blockIdx.x ? st->tile_eq[tid] : 0u, wave_tot, eq_seen);
+    block_exclusive_scan(gt_before, wave_tot, gt_seen);
+    block_exclusive_scan(eq_before, wave_tot, eq_seen);
     uint32_t written = gt_seen + min(eq_seen, take);
-    const int64_t lo = (int64_t)blockIdx.x * tile, hi = min(lo + tile, total);
     for (int64_t c0 = lo; c0 < hi; c0 += SEL_THREADS) {
         const int64_t c = c0 + tid;
-        const uint32_t k = c < hi ? keys[c] : 0u;
+        const uint32_t k = c < hi ? next : 0u;
+        next = keys[min(c + SEL_THREADS, total - 1)];
         const uint32_t is_eq = (c < hi && k == thr) ? 1u : 0u;
         // both counts of a chunk fit 16 bits: one scan finds them together
         const uint32_t is_gt = (c < hi && k > thr) ? 1u : 0u;
@@ -271,17 +300,6 @@ __global__ __launch_bounds__(SEL_THREADS) void select_emit_kernel(const uint32_t
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// The layer offsets come from a host array that may be gone when the call returns, and the call
-// must neither block nor stage a copy: they travel as kernel arguments, 128 at a time.
-struct OffsetChunk {
-    int64_t v[128];
-};
-__global__ void select_offsets_kernel(int64_t *dst, int n, OffsetChunk c)
-{
-    const int t = threadIdx.x;
-    if (t < n) dst[t] = c.v[t];
-}
-
 }  // namespace
 
 int launch_channel_salience(const void *W, const void *Gr, int N, int K, float weight, int accumulate, float *salience,
@@ -304,13 +322,16 @@ int launch_select_salient(const float *salience, const int64_t *layer_offsets_ho
     SelectState *state = (SelectState *)workspace;
     int64_t *offsets = (int64_t *)((uint8_t *)workspace + align_up(sizeof(SelectState), 256));
     const int64_t total = layer_offsets_host[L];
-    hipLaunchKernelGGL(select_init_kernel, dim3((SEL_PASSES * SEL_BINS + 255) / 256), dim3(256), 0, st, state, (uint32_t)T, layer_counts, L);
-    if (T == 0) return (int)hipGetLastError();   // every list is empty
     for (int o = 0; o <= L; o += 128) {
         OffsetChunk c;
         const int n = std::min(128, L + 1 - o);
         for (int i = 0; i < 128; ++i) c.v[i] = i < n ? layer_offsets_host[o + i] : 0;
-        hipLaunchKernelGGL(select_offsets_kernel, dim3(1), dim3(128), 0, st, offsets + o, n, c);
+        if (o == 0) {
+            hipLaunchKernelGGL(select_init_kernel, dim3((SEL_PASSES * SEL_BINS + 255) / 256), dim3(256), 0, st, state, (uint32_t)T,
+                               layer_counts, L, offsets, n, c);
+            if (T == 0) return (int)hipGetLastError();   // every list is empty
+        } else
+            hipLaunchKernelGGL(select_offsets_kernel, dim3(1), dim3(128), 0, st, offsets + o, n, c);
     }
     const uint32_t *keys = (const uint32_t *)salience;
     const dim3 threads(SEL_THREADS);
