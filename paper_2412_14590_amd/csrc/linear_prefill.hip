@@ -24,12 +24,17 @@
 //    sustains at full MFMA rate), and the A fragment of slot s+6 (s+4 with two token tiles per
 //    wave) is requested at slot s (LDS latency is several MFMAs long).  The pipeline runs across group boundaries; the only
 //    block-wide barrier sits in the middle of a group (slot TM*2), where the next group's
-//    activations are known to have landed and the stage of the previous group is released.
+//    activations are known to have landed and the stage of the previous group is released; the
+//    requests it sets free go out one at a time over the slots behind it.
 //  * Group metadata (4 fp16 scales, 4 zero points) is fetched once per 4 groups.
+//  * Activation scales per (token, group): the products of both scales of a tile come from one
+//    bf16 MFMA, in the accumulators' layout.
 //  * Epilogue: token scale (from LDS, where the prologue left the block's), fp16
 //    conversion, scatter to the original channel (Sec. 3.4).
 // 8-bit and 4-bit channel tiles are different block ranges of one launch; where the grid of output
-// tiles is short and K long, K is split over blocks and a second kernel adds the parts.
+// tiles is short and K long, K is split over blocks and a second kernel adds the parts.  On small grids
+// the same block functions run with one wave to a tile and K cut over the waves of a block
+// (linear_slices_kernel).
 #include <algorithm>
 #include <cstdlib>
 #include <mutex>
