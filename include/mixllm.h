@@ -57,8 +57,9 @@ enum {
 
 /* Kernel selection for the entry points that take a `path` argument. */
 enum {
-    MIXLLM_PATH_AUTO = 0,    /* decode path for M <= 16; 17..64 tokens: the path for a few dozen tokens or the tiled path,
-                                whichever measured faster for the shape; tiled MFMA path otherwise */
+    MIXLLM_PATH_AUTO = 0,    /* decode path for M <= 16; from 17 tokens on small grids, tiles of 32 x 32 cut along K over the
+                                waves of a block (no path of its own); else up to 64 tokens the path for a few dozen tokens
+                                or the tiled path, whichever measured faster for the shape; tiled MFMA path otherwise */
     MIXLLM_PATH_GENERIC = 1, /* one thread per output element, no MFMA; any shape; slow */
     MIXLLM_PATH_DECODE = 2,  /* weight-streaming path, M <= 16; picks one of the three variants below */
     MIXLLM_PATH_PREFILL = 3, /* LDS-staged tiled MFMA path, any M */
