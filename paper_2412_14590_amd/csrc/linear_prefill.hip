@@ -1249,7 +1249,9 @@ int launch_linear_prefill(const LinearParams &p0, hipStream_t st)
 // blocks: 14.7 against 14.0; at 128, 776 blocks: 15.6 against 14.1).  A long K is a long chain again: with two blocks on a
 // CU the line lies at K = 8192 (64 tokens, N = 8192: 21.7 against 25.2; K = 14336, N = 4096 at 100 tokens 30 against 24.7, K
 // split over blocks), with one at K = 14336 (N = 4096 at 20 tokens 17.8 against 19.4; N = 1000 at 130 13.4 against 17.8;
-// K = 28672, N = 2000 at 60 tokens 31 against 27).  Up to 16 tokens the decode kernels are ahead (K = N = 4096: 7.2 against
+// K = 28672, N = 2000 at 60 tokens 31 against 27).  With one token tile the path for a few dozen tokens reads the weights
+// evenly, and where CUs would get a second block it is level or ahead (32 tokens, N = 8192, 258 blocks: 11.4 against 12.2 at K =
+// 4096, 18.2 against 19.8 at K = 8192).  Up to 16 tokens the decode kernels are ahead (K = N = 4096: 7.2 against
 // 7.8).  Beyond 64 tokens a call that brings the scratch to split K over blocks gets that split, and with it the same sums
 // as from the tiled path by name.
 bool slices_pay(const LinearParams &p)
@@ -1257,7 +1259,7 @@ bool slices_pay(const LinearParams &p)
     if (p.P || p.S || p.M <= 16 || p.ng < 4 * SLICES - 3 || !prefill_covers(p)) return false;
     if (p.M > 64 && prefill_would_split(p)) return false;
     const long blocks = (long)((p.M + 31) / 32) * ((p.ntiles8 + 1) / 2 + (p.ntiles4 + 1) / 2), cus = cu_count();
-    return blocks <= cus ? p.ng <= 112 : blocks <= 2 * cus + cus / 16 && p.ng <= 64;
+    return blocks <= cus ? p.ng <= 112 : p.M > 32 && blocks <= 2 * cus + cus / 16 && p.ng <= 64;
 }
 
 int launch_linear_slices(const LinearParams &p, hipStream_t st)

@@ -465,7 +465,7 @@ def test_tiled_path_with_k_split_over_blocks(M, K, N, n8, variant):
 @pytest.mark.parametrize("M,K,N,n8", [
     (17, 1664, 16, 3), (32, 1664, 33, 33), (33, 1920, 70, 0), (65, 4224, 64, 6),      # 4 quads (one of 1 and of 3 groups), 9: uneven shares
     (17, 14336, 300, 30), (300, 4096, 257, 26), (64, 8192, 1000, 100),                # the longest K it takes; many token tiles
-    (40, 1920, 4095, 409), (32, 2048, 8192, 31), (48, 2048, 8448, 0), (48, 2048, 8449, 0)])   # around one and two blocks a CU
+    (40, 1920, 4095, 409), (32, 2048, 8160, 31), (32, 2048, 8192, 31), (48, 2048, 8448, 0), (48, 2048, 8449, 0)])   # around one and two blocks a CU
 def test_tiles_cut_along_k_over_the_waves_of_a_block(M, K, N, n8, variant):
     # Small grids (the library's choice, no path of its own): four waves of a block take a quarter of K each and add
     # their sums up in LDS.  Against the oracle by row norm and per element, bit-identical between runs and between the
