@@ -155,6 +155,7 @@ PyObject *py_mixed_linear(PyObject *, PyObject *const *a, Py_ssize_t n)
         int rc;
         {
             pybind11::gil_scoped_release no_gil;
+            if (!xq.defined() || xq.dim() != 2) throw Refused{"xq: a matrix"};
             const int64_t M = xq.size(0), K = xq.size(1);
             if (K != L.K || xs.size(0) != M) throw Refused{"xq, xs and the layer agree in their sizes"};
             if (xs.size(1) == 0) throw Refused{"xs has a column"};

@@ -7,6 +7,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 import paper_2412_14590_amd as mx
 from paper_2412_14590_amd import binding
@@ -163,3 +164,18 @@ def test_build_scan_flags_a_register_used_between_its_hand_issued_load_and_the_w
     build.check_hand_issued_loads(branchy, "branchy")
     lds = ok.replace("global_load_dwordx2 v[104:105], v119, s[98:99]", "global_load_lds_dwordx4 v104, s[98:99]")
     build.check_hand_issued_loads(lds.replace("v_add_u32_e32 v1, v2, v3", "v_mov_b32_e32 v104, 0"), "lds")
+
+
+def layer_arguments(K=256, N=40, n8=4):
+    """A packed layer without data as the native calls take it: with no tokens nothing of it is read, and no GPU is needed."""
+    return (K, N, n8, K, *[torch.empty(0, dtype=torch.uint8) for _ in range(6)])
+
+
+def test_native_linear_takes_matrices_only():
+    call = lambda xq: binding._calls().mixed_linear(xq, torch.empty((xq.shape[0], 1), dtype=torch.float16), *layer_arguments(),
+                                                    mx.PATH_AUTO, None, None, 0)
+    y = call(torch.empty((0, 256), dtype=torch.int8))
+    assert y.shape == (0, 40) and y.dtype == torch.float16
+    for shape in ((0, 256, 1), (0, 256, 3), (0, 256, 0)):
+        with pytest.raises(AssertionError):
+            call(torch.empty(shape, dtype=torch.int8))
