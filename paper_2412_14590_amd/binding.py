@@ -241,8 +241,7 @@ def unpack_weights(L: PackedLayer) -> dict:
 
 def quantize_activations(x: torch.Tensor, act_group=None, out=None):
     """fp16 x [M,K] -> (xq int8 [M,K], xscale fp16 [M, K/act_group])."""
-    xq, xs = (None, None) if out is None else out
-    return _result(_calls().quantize_activations(x, act_group, xq, xs, _stream()), "mixllm_quantize_activations")
+    return _result(_calls().quantize_activations(x, act_group, out, _stream()), "mixllm_quantize_activations")
 
 
 def mixed_linear(xq: torch.Tensor, xs: torch.Tensor, L: PackedLayer, path: int = PATH_AUTO, out=None, workspace=None):

@@ -15,6 +15,8 @@
 
 namespace {
 
+namespace py = pybind11;
+
 decltype(&mixllm_query_sizes) query_sizes;
 decltype(&mixllm_quantize_activations) quantize_activations;
 decltype(&mixllm_mixed_linear_path) mixed_linear_path;
@@ -90,7 +92,7 @@ PyObject *py_linear_fp16(PyObject *, PyObject *const *a, Py_ssize_t n)
         void *stream = PyLong_AsVoidPtr(a[14]);
         int rc;
         {
-            pybind11::gil_scoped_release no_gil;
+            py::gil_scoped_release no_gil;
             half_matrix(x);
             if (x.size(1) != L.K) throw Refused{"x has as many columns as the layer has inputs"};
             const mixllm_desc d{(int32_t)x.size(0), L.K, L.N, L.n8, MIXLLM_GROUP, act_group, L.w8_group};
@@ -109,24 +111,32 @@ PyObject *py_linear_fp16(PyObject *, PyObject *const *a, Py_ssize_t n)
     });
 }
 
-// quantize_activations(x, act_group or None, xq, xs, stream) -> (xq, xs), or a status
+// quantize_activations(x, act_group or None, (xq, xs) or None, stream) -> (xq, xs), or a status.  Only where no buffers are
+// given at all are they allocated: one that is missing from a pair is refused by the library.
 PyObject *py_quantize_activations(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    return run(n, 5, [&]() -> PyObject * {
+    return run(n, 4, [&]() -> PyObject * {
         const at::Tensor x = tensor(a[0]);
         int32_t act_group = a[1] == Py_None ? 0 : small(a[1]);
-        const bool per_token = a[1] == Py_None;
-        at::Tensor xq = tensor(a[2]), xs = tensor(a[3]);
-        void *stream = PyLong_AsVoidPtr(a[4]);
+        const bool per_token = a[1] == Py_None, allocate = a[2] == Py_None;
+        at::Tensor xq, xs;
+        if (!allocate) {
+            const py::object out = py::reinterpret_steal<py::object>(PySequence_Tuple(a[2]));
+            if (!out) throw python_error();
+            TORCH_CHECK_VALUE(PyTuple_GET_SIZE(out.ptr()) == 2, "out: two buffers, got ", PyTuple_GET_SIZE(out.ptr()));
+            xq = tensor(PyTuple_GET_ITEM(out.ptr(), 0));
+            xs = tensor(PyTuple_GET_ITEM(out.ptr(), 1));
+        }
+        void *stream = PyLong_AsVoidPtr(a[3]);
         int rc;
         {
-            pybind11::gil_scoped_release no_gil;
+            py::gil_scoped_release no_gil;
             half_matrix(x);
             const int32_t M = (int32_t)x.size(0), K = (int32_t)x.size(1);
-            if (!xq.defined()) xq = x.new_empty({M, K}, x.options().dtype(at::kChar));
             if (per_token) act_group = K;
-            if (!xs.defined()) {
+            if (allocate) {
                 if (act_group <= 0) throw Refused{"act_group is positive"};
+                xq = x.new_empty({M, K}, x.options().dtype(at::kChar));
                 xs = x.new_empty({M, K / act_group});
             }
             const mixllm_desc d{M, K, 1, 0, MIXLLM_GROUP, act_group, K};
@@ -154,7 +164,7 @@ PyObject *py_mixed_linear(PyObject *, PyObject *const *a, Py_ssize_t n)
         void *stream = PyLong_AsVoidPtr(a[15]);
         int rc;
         {
-            pybind11::gil_scoped_release no_gil;
+            py::gil_scoped_release no_gil;
             if (!xq.defined() || xq.dim() != 2) throw Refused{"xq: a matrix"};
             const int64_t M = xq.size(0), K = xq.size(1);
             if (K != L.K || xs.size(0) != M) throw Refused{"xq, xs and the layer agree in their sizes"};

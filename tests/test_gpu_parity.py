@@ -614,6 +614,15 @@ def test_calls_from_python_check_their_arguments_and_return_the_callers_tensors(
     assert empty.shape == (0, 64) and empty.dtype == torch.float16
 
 
+def test_quantizer_refuses_a_missing_buffer():
+    x = torch.ones((3, 256), dtype=torch.float16, device="cuda")
+    xq, xs = mx.quantize_activations(x)
+    for out in ((None, xs), (xq, None), (None, None)):
+        with pytest.raises(mx.MixllmError) as e:
+            mx.quantize_activations(x, out=out)
+        assert e.value.status == -1
+
+
 def test_fused_entry_point_rejects_a_short_workspace():
     W, sal, L, x, xq, xs = make_case(40, 512, 64, 6, seed=32)
     PL = pack_from_oracle(L)

@@ -179,3 +179,16 @@ def test_native_linear_takes_matrices_only():
     for shape in ((0, 256, 1), (0, 256, 3), (0, 256, 0)):
         with pytest.raises(AssertionError):
             call(torch.empty(shape, dtype=torch.int8))
+
+
+def test_native_quantizer_allocates_only_where_no_buffers_are_given():
+    x, q, s = (torch.empty((0, 256), dtype=t) for t in (torch.float16, torch.int8, torch.float16))
+    call = lambda out: binding._calls().quantize_activations(x, None, out, 0)
+    got = call(None)
+    assert got[0].dtype == torch.int8 and got[0].shape == (0, 256) and got[1].dtype == torch.float16 and got[1].shape == (0, 1)
+    got = call([q, s])
+    assert got[0] is q and got[1] is s
+    assert call((None, s)) == (None, s) and call((q, None)) == (q, None)      # no tokens: nothing is written, nothing was allocated
+    for bad in ((q,), (q, s, s)):
+        with pytest.raises(ValueError):
+            call(bad)
