@@ -42,11 +42,20 @@ void *address(const at::Tensor &t)
     return t.data_ptr();
 }
 
-int32_t small(PyObject *o)
+int32_t index(PyObject *o)
 {
     const long v = PyLong_AsLong(o);
     if (v == -1 && PyErr_Occurred()) throw python_error();
     return (int32_t)v;
+}
+
+// a descriptor's field: whatever int() makes a number of
+int32_t number(PyObject *o)
+{
+    if (PyLong_CheckExact(o)) return index(o);
+    const py::object i = py::reinterpret_steal<py::object>(PyNumber_Long(o));
+    if (!i) throw python_error();
+    return index(i.ptr());
 }
 
 // K, N, n8, w8_group, w8, w4, s8, s4, z4, perm of a packed layer, as they stand in the arguments
@@ -54,7 +63,7 @@ struct Layer {
     int32_t K, N, n8, w8_group;
     at::Tensor w8, w4, s8, s4, z4, perm;
     explicit Layer(PyObject *const *a)
-        : K(small(a[0])), N(small(a[1])), n8(small(a[2])), w8_group(small(a[3])), w8(tensor(a[4])), w4(tensor(a[5])), s8(tensor(a[6])),
+        : K(number(a[0])), N(number(a[1])), n8(number(a[2])), w8_group(number(a[3])), w8(tensor(a[4])), w4(tensor(a[5])), s8(tensor(a[6])),
           s4(tensor(a[7])), z4(tensor(a[8])), perm(tensor(a[9]))
     {
     }
@@ -87,7 +96,7 @@ PyObject *py_linear_fp16(PyObject *, PyObject *const *a, Py_ssize_t n)
     return run(n, 15, [&]() -> PyObject * {
         const at::Tensor x = tensor(a[0]);
         const Layer L(a + 1);
-        const int32_t act_group = small(a[11]);
+        const int32_t act_group = number(a[11]);
         at::Tensor y = tensor(a[12]), ws = tensor(a[13]);
         void *stream = PyLong_AsVoidPtr(a[14]);
         int rc;
@@ -117,8 +126,8 @@ PyObject *py_quantize_activations(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return run(n, 4, [&]() -> PyObject * {
         const at::Tensor x = tensor(a[0]);
-        int32_t act_group = a[1] == Py_None ? 0 : small(a[1]);
         const bool per_token = a[1] == Py_None, allocate = a[2] == Py_None;
+        int32_t act_group = per_token ? 0 : allocate ? index(a[1]) : number(a[1]);   // (a tensor's size is an integer)
         at::Tensor xq, xs;
         if (!allocate) {
             const py::object out = py::reinterpret_steal<py::object>(PySequence_Tuple(a[2]));
@@ -158,7 +167,7 @@ PyObject *py_mixed_linear(PyObject *, PyObject *const *a, Py_ssize_t n)
     return run(n, 16, [&]() -> PyObject * {
         const at::Tensor xq = tensor(a[0]), xs = tensor(a[1]);
         const Layer L(a + 2);
-        const int32_t path = small(a[12]);
+        const int32_t path = index(a[12]);
         at::Tensor y = tensor(a[13]);
         const at::Tensor ws = tensor(a[14]);
         void *stream = PyLong_AsVoidPtr(a[15]);

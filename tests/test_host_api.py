@@ -192,3 +192,21 @@ def test_native_quantizer_allocates_only_where_no_buffers_are_given():
     for bad in ((q,), (q, s, s)):
         with pytest.raises(ValueError):
             call(bad)
+
+
+def test_native_calls_take_whole_numbers_of_any_type():
+    # descriptors were always filled through int(): numpy integers, and floats that are whole
+    x, xs = torch.empty((0, 256), dtype=torch.float16), torch.empty((0, 1), dtype=torch.float16)
+    K, N, n8, w8_group, *buffers = layer_arguments()
+    for t in (int, float, np.int64, np.float32):
+        y = binding._calls().linear_fp16(x, t(K), t(N), t(n8), t(w8_group), *buffers, t(128), None, None, 0)
+        assert y.shape == (0, N)
+        y = binding._calls().mixed_linear(x.to(torch.int8), xs, t(K), t(N), t(n8), t(w8_group), *buffers, mx.PATH_AUTO, None, None, 0)
+        assert y.shape == (0, N)
+        binding._calls().quantize_activations(x, t(128), (x.to(torch.int8), xs), 0)
+    with pytest.raises(TypeError):
+        binding._calls().linear_fp16(x, *layer_arguments(), [128], None, None, 0)
+    with pytest.raises(TypeError):                     # ... nor a size to allocate by
+        binding._calls().quantize_activations(x, 128.0, None, 0)
+    with pytest.raises(TypeError):                     # the kernel selection is no descriptor field: an integer as before
+        binding._calls().mixed_linear(x.to(torch.int8), xs, *layer_arguments(), 0.0, None, None, 0)
