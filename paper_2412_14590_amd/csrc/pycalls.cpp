@@ -8,6 +8,8 @@
 #include <Python.h>
 
 #include <ATen/ATen.h>
+#include <ATen/PythonTorchFunctionTLS.h>
+#include <torch/csrc/DynamicTypes.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -74,6 +76,18 @@ void half_matrix(const at::Tensor &x)
     if (!x.defined() || x.scalar_type() != at::kHalf || x.dim() != 2) throw Refused{"x: an fp16 matrix"};
 }
 
+// A subclass of Tensor, or a mode, may have a new_empty of its own: results are then allocated by it, so that they are of
+// the type they would have in Python.
+bool overrides_new_empty(PyObject *o)
+{
+    return !THPVariable_CheckExact(o) || at::impl::torch_function_mode_enabled();
+}
+at::Tensor new_empty_in_python(PyObject *o, int64_t rows, int64_t columns, at::ScalarType type)
+{
+    const auto dtype = py::reinterpret_borrow<py::object>((PyObject *)torch::getTHPDtype(type));
+    return tensor(py::handle(o).attr("new_empty")(py::make_tuple(rows, columns), py::arg("dtype") = dtype).ptr());
+}
+
 // f() with its C++ exceptions as Python ones.  The calls below release the interpreter while they allocate and launch; a
 // status other than MIXLLM_OK comes back as a number.
 template <typename F>
@@ -99,11 +113,12 @@ PyObject *py_linear_fp16(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int32_t act_group = number(a[11]);
         at::Tensor y = tensor(a[12]), ws = tensor(a[13]);
         void *stream = PyLong_AsVoidPtr(a[14]);
+        half_matrix(x);
+        if (x.size(1) != L.K) throw Refused{"x has as many columns as the layer has inputs"};
+        if (!y.defined() && overrides_new_empty(a[0])) y = new_empty_in_python(a[0], x.size(0), L.N, at::kHalf);
         int rc;
         {
             py::gil_scoped_release no_gil;
-            half_matrix(x);
-            if (x.size(1) != L.K) throw Refused{"x has as many columns as the layer has inputs"};
             const mixllm_desc d{(int32_t)x.size(0), L.K, L.N, L.n8, MIXLLM_GROUP, act_group, L.w8_group};
             if (!y.defined()) y = x.new_empty({x.size(0), L.N});
             rc = MIXLLM_OK;
@@ -137,14 +152,18 @@ PyObject *py_quantize_activations(PyObject *, PyObject *const *a, Py_ssize_t n)
             xs = tensor(PyTuple_GET_ITEM(out.ptr(), 1));
         }
         void *stream = PyLong_AsVoidPtr(a[3]);
+        half_matrix(x);
+        const int32_t M = (int32_t)x.size(0), K = (int32_t)x.size(1);
+        if (per_token) act_group = K;
+        if (allocate && act_group <= 0) throw Refused{"act_group is positive"};
+        if (allocate && overrides_new_empty(a[0])) {
+            xq = new_empty_in_python(a[0], M, K, at::kChar);
+            xs = new_empty_in_python(a[0], M, K / act_group, at::kHalf);
+        }
         int rc;
         {
             py::gil_scoped_release no_gil;
-            half_matrix(x);
-            const int32_t M = (int32_t)x.size(0), K = (int32_t)x.size(1);
-            if (per_token) act_group = K;
-            if (allocate) {
-                if (act_group <= 0) throw Refused{"act_group is positive"};
+            if (allocate && !xq.defined()) {
                 xq = x.new_empty({M, K}, x.options().dtype(at::kChar));
                 xs = x.new_empty({M, K / act_group});
             }
@@ -171,13 +190,14 @@ PyObject *py_mixed_linear(PyObject *, PyObject *const *a, Py_ssize_t n)
         at::Tensor y = tensor(a[13]);
         const at::Tensor ws = tensor(a[14]);
         void *stream = PyLong_AsVoidPtr(a[15]);
+        if (!xq.defined() || xq.dim() != 2) throw Refused{"xq: a matrix"};
+        const int64_t M = xq.size(0), K = xq.size(1);
+        if (K != L.K || xs.size(0) != M) throw Refused{"xq, xs and the layer agree in their sizes"};
+        if (xs.size(1) == 0) throw Refused{"xs has a column"};
+        if (!y.defined() && overrides_new_empty(a[0])) y = new_empty_in_python(a[0], M, L.N, at::kHalf);
         int rc;
         {
             py::gil_scoped_release no_gil;
-            if (!xq.defined() || xq.dim() != 2) throw Refused{"xq: a matrix"};
-            const int64_t M = xq.size(0), K = xq.size(1);
-            if (K != L.K || xs.size(0) != M) throw Refused{"xq, xs and the layer agree in their sizes"};
-            if (xs.size(1) == 0) throw Refused{"xs has a column"};
             if (!y.defined()) y = xq.new_empty({M, L.N}, xq.options().dtype(at::kHalf));
             const mixllm_desc d{(int32_t)M, L.K, L.N, L.n8, MIXLLM_GROUP, (int32_t)(K / xs.size(1)), L.w8_group};
             rc = mixed_linear_path(&d, (const int8_t *)address(xq), address(xs), address(L.w4), address(L.w8), address(L.s4), address(L.s8),

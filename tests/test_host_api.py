@@ -210,3 +210,37 @@ def test_native_calls_take_whole_numbers_of_any_type():
         binding._calls().quantize_activations(x, 128.0, None, 0)
     with pytest.raises(TypeError):                     # the kernel selection is no descriptor field: an integer as before
         binding._calls().mixed_linear(x.to(torch.int8), xs, *layer_arguments(), 0.0, None, None, 0)
+
+
+class Tagged(torch.Tensor):
+    """A tensor subclass: its methods' results are of its type."""
+
+
+def test_native_calls_allocate_results_through_the_activations_own_new_empty():
+    # ... where new_empty is overridden (a subclass, a mode); plain tensors take the short way
+    from torch.overrides import TorchFunctionMode
+    xs = torch.empty((0, 1), dtype=torch.float16)
+
+    def results(x):
+        c = binding._calls()
+        yield c.linear_fp16(x, *layer_arguments(), 256, None, None, 0)
+        yield c.mixed_linear(x.to(torch.int8), xs, *layer_arguments(), mx.PATH_AUTO, None, None, 0)
+        yield from c.quantize_activations(x, None, None, 0)
+
+    x = torch.empty((0, 256), dtype=torch.float16)
+    want = [((0, 40), torch.float16), ((0, 40), torch.float16), ((0, 256), torch.int8), ((0, 1), torch.float16)]
+    for kind in (torch.Tensor, Tagged):
+        got = list(results(x.as_subclass(kind)))
+        assert [type(t) for t in got] == [kind] * 4 and [(tuple(t.shape), t.dtype) for t in got] == want
+    assert type(next(results(torch.nn.Parameter(x)))) is torch.Tensor
+
+    class Seen(TorchFunctionMode):
+        count = 0
+
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            self.count += func is torch.Tensor.new_empty
+            return func(*args, **(kwargs or {}))
+
+    with Seen() as mode:
+        assert len(list(results(x))) == 4
+    assert mode.count >= 4
