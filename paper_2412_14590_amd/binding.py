@@ -254,6 +254,7 @@ def mixed_linear(xq: torch.Tensor, xs: torch.Tensor, L: PackedLayer, path: int =
 def debug_group_partials(xq: torch.Tensor, L: PackedLayer, path: int = PATH_AUTO) -> torch.Tensor:
     """Exact int32 partial sums P [M,N,K/128] (original channel order) from the chosen path."""
     M, K = xq.shape
+    assert K == L.K
     P = torch.empty((M, L.N, K // GROUP), dtype=torch.int32, device=xq.device)
     d = L.desc(M)
     _check(lib().mixllm_debug_group_partials(C.byref(d), _ptr(xq), _ptr(L.w4), _ptr(L.w8), _ptr(L.z4),
@@ -266,6 +267,7 @@ def debug_channel_sums(xq: torch.Tensor, xs: torch.Tensor, L: PackedLayer, path:
     """S [M,N] int32 = the per-group partial sums added up over the groups, from the kernels the
     linear launches for this shape (generic or tiled path)."""
     M, K = xq.shape
+    assert K == L.K
     S = torch.empty((M, L.N), dtype=torch.int32, device=xq.device)
     d = L.desc(M, K // xs.shape[1])
     _check(lib().mixllm_debug_channel_sums(C.byref(d), _ptr(xq), _ptr(xs), _ptr(L.w4), _ptr(L.w8), _ptr(L.s4),
@@ -293,7 +295,8 @@ def linear_fp16(x: torch.Tensor, L: PackedLayer, act_group=None, out=None, works
 def linear_fp16_static(x: torch.Tensor, L: PackedLayer, out: torch.Tensor, act_group=None) -> torch.Tensor:
     """mixllm_mixed_linear_fp16_static: the same as linear_fp16 with the scratch inside the library; the
     caller brings the output tensor, and nothing is allocated on the way."""
-    assert x.dtype == torch.float16 and x.dim() == 2 and out.dtype == torch.float16 and out.shape == (x.shape[0], L.N)
+    assert x.dtype == torch.float16 and x.dim() == 2 and x.shape[1] == L.K
+    assert out.dtype == torch.float16 and out.shape == (x.shape[0], L.N)
     d = L.desc(x.shape[0], act_group)
     _check(lib().mixllm_mixed_linear_fp16_static(C.byref(d), _ptr(x), _ptr(L.w4), _ptr(L.w8), _ptr(L.s4), _ptr(L.s8),
                                                  _ptr(L.z4), _ptr(L.perm), _ptr(out), _stream()),

@@ -76,6 +76,15 @@ void half_matrix(const at::Tensor &x)
     if (!x.defined() || x.scalar_type() != at::kHalf || x.dim() != 2) throw Refused{"x: an fp16 matrix"};
 }
 
+// A buffer of the caller's holds `n` values of `type`, or the same number of integers of that width (raw bits): what the
+// kernels read and write goes by the sizes of the call alone.  A missing buffer is left to the library.
+void holds(const at::Tensor &t, at::ScalarType type, int64_t n, const char *what)
+{
+    if (!t.defined()) return;
+    const bool bits = at::isIntegralType(t.scalar_type(), /*includeBool=*/true) && t.itemsize() == (int64_t)at::elementSize(type);
+    if ((t.scalar_type() != type && !bits) || t.numel() < n) throw Refused{what};
+}
+
 // A subclass of Tensor, or a mode, may have a new_empty of its own: results are then allocated by it, so that they are of
 // the type they would have in Python.
 bool overrides_new_empty(PyObject *o)
@@ -104,6 +113,9 @@ PyObject *run(Py_ssize_t n, Py_ssize_t expected, F &&f)
     END_HANDLE_TH_ERRORS
 }
 
+// (A workspace's element count stands for its bytes: exact for the uint8 tensor it is meant to be, short of them, never
+// beyond, for any other.)
+
 // linear_fp16(x, <layer>, act_group, out, workspace, stream) -> y, or a status
 PyObject *py_linear_fp16(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
@@ -114,6 +126,7 @@ PyObject *py_linear_fp16(PyObject *, PyObject *const *a, Py_ssize_t n)
         at::Tensor y = tensor(a[12]), ws = tensor(a[13]);
         void *stream = PyLong_AsVoidPtr(a[14]);
         half_matrix(x);
+        holds(y, at::kHalf, x.size(0) * L.N, "y: an fp16 buffer of tokens x outputs");
         if (x.size(1) != L.K) throw Refused{"x has as many columns as the layer has inputs"};
         if (!y.defined() && overrides_new_empty(a[0])) y = new_empty_in_python(a[0], x.size(0), L.N, at::kHalf);
         int rc;
@@ -155,6 +168,8 @@ PyObject *py_quantize_activations(PyObject *, PyObject *const *a, Py_ssize_t n)
         half_matrix(x);
         const int32_t M = (int32_t)x.size(0), K = (int32_t)x.size(1);
         if (per_token) act_group = K;
+        holds(xq, at::kChar, (int64_t)M * K, "xq: an int8 buffer of tokens x inputs");
+        if (act_group > 0) holds(xs, at::kHalf, (int64_t)M * (K / act_group), "xs: an fp16 buffer of tokens x groups");
         if (allocate && act_group <= 0) throw Refused{"act_group is positive"};
         if (allocate && overrides_new_empty(a[0])) {
             xq = new_empty_in_python(a[0], M, K, at::kChar);
@@ -194,12 +209,20 @@ PyObject *py_mixed_linear(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int64_t M = xq.size(0), K = xq.size(1);
         if (K != L.K || xs.size(0) != M) throw Refused{"xq, xs and the layer agree in their sizes"};
         if (xs.size(1) == 0) throw Refused{"xs has a column"};
+        const int32_t act_group = (int32_t)(K / xs.size(1));
+        holds(xq, at::kChar, M * K, "xq: an int8 matrix");
+        if (act_group == K || act_group == MIXLLM_GROUP) {
+            // as many scales as the library reads: 129 columns for 130 groups also divide to groups of 128
+            holds(xs, at::kHalf, M * (K / act_group), "xs: fp16 scales, tokens x groups");
+            if (xs.numel() != M * (K / act_group)) throw Refused{"xs: one scale per token and group"};
+        }
+        holds(y, at::kHalf, M * L.N, "y: an fp16 buffer of tokens x outputs");
         if (!y.defined() && overrides_new_empty(a[0])) y = new_empty_in_python(a[0], M, L.N, at::kHalf);
         int rc;
         {
             py::gil_scoped_release no_gil;
             if (!y.defined()) y = xq.new_empty({M, L.N}, xq.options().dtype(at::kHalf));
-            const mixllm_desc d{(int32_t)M, L.K, L.N, L.n8, MIXLLM_GROUP, (int32_t)(K / xs.size(1)), L.w8_group};
+            const mixllm_desc d{(int32_t)M, L.K, L.N, L.n8, MIXLLM_GROUP, act_group, L.w8_group};
             rc = mixed_linear_path(&d, (const int8_t *)address(xq), address(xs), address(L.w4), address(L.w8), address(L.s4), address(L.s8),
                                    address(L.z4), (const int32_t *)address(L.perm), address(y), address(ws),
                                    ws.defined() ? (size_t)ws.numel() : 0, path, stream);

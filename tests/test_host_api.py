@@ -244,3 +244,46 @@ def test_native_calls_allocate_results_through_the_activations_own_new_empty():
     with Seen() as mode:
         assert len(list(results(x))) == 4
     assert mode.count >= 4
+
+
+def test_native_calls_refuse_buffers_that_do_not_hold_what_is_read_or_written():
+    # device buffers: their sizes and types are looked at before their address, so host tensors will do
+    c, h, i8 = binding._calls(), torch.float16, torch.int8
+    K, N, M = 256, 40, 3
+    new = lambda *size, dtype=h: torch.empty(size, dtype=dtype)
+
+    def refused(match, f):
+        with pytest.raises(AssertionError, match=match):
+            f()
+
+    fp16 = lambda out: c.linear_fp16(new(M, K), *layer_arguments(), K, out, None, 0)
+    linear = lambda xq, xs, out: c.mixed_linear(xq, xs, *layer_arguments(), mx.PATH_AUTO, out, None, 0)
+    quant = lambda q, s, g=None: c.quantize_activations(new(M, K), g, (q, s), 0)
+    for out in (new(M, N - 1), new(M * N - 1), new(M, N, dtype=torch.float32), new(M, N, dtype=torch.bfloat16), new(2 * M, N, dtype=torch.int8)):
+        refused("^y", lambda: fp16(out))
+        refused("^y", lambda: linear(new(M, K, dtype=i8), new(M, 1), out))
+    for xq in (new(M, K), new(M, K, dtype=torch.float8_e4m3fn), new(M, K, dtype=torch.int32)):
+        refused("^xq", lambda: linear(xq, new(M, 1), new(M, N)))
+    refused("^xs", lambda: linear(new(M, K, dtype=i8), new(M, 1, dtype=torch.float32), new(M, N)))
+    refused("^xs", lambda: linear(new(M, K, dtype=i8), new(M, 1, 2), new(M, N)))
+    wide = 128 * 130                                   # 129 columns of scales divide to groups of 128 and are one column short
+    refused("^xs", lambda: c.mixed_linear(new(M, wide, dtype=i8), new(M, 129), *layer_arguments(K=wide), mx.PATH_AUTO, new(M, N), None, 0))
+    for q, s, g in ((new(M, K - 1, dtype=i8), new(M, 1), None), (new(M, K), new(M, 1), None), (new(M, K, dtype=i8), new(M - 1, 1), None),
+                    (new(M, K, dtype=i8), new(M, 1), 128), (new(M, K, dtype=i8), new(M, 1, dtype=torch.float32), None)):
+        refused("^x[qs]", lambda: quant(q, s, g))
+    # room to spare, another shape and the raw bits as integers were always taken: these get as far as the address
+    for out in (new(M, N), new(M * N + 7), new(M, N, dtype=torch.int16)):
+        refused("device", lambda: fp16(out))
+        refused("device", lambda: linear(new(M, K, dtype=torch.uint8), new(M, 1, dtype=torch.int16), out))
+    refused("device", lambda: quant(new(M, K, dtype=torch.uint8), new(4 * M), None))
+
+
+def test_static_entry_and_debug_hooks_refuse_activations_of_another_width():
+    L = binding.PackedLayer(*layer_arguments())
+    for K in (128, 384):
+        x, xs = torch.empty((3, K), dtype=torch.float16), torch.empty((3, 1), dtype=torch.float16)
+        for call in (lambda: mx.linear_fp16_static(x, L, torch.empty((3, 40), dtype=torch.float16)),
+                     lambda: mx.debug_group_partials(x.to(torch.int8), L), lambda: mx.debug_channel_sums(x.to(torch.int8), xs, L)):
+            with pytest.raises(AssertionError) as e:
+                call()
+            assert "device" not in str(e.value)        # refused for its width, before any address is taken
