@@ -13,8 +13,8 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef _Float16 half_t;
+typedef half_t v8h __attribute__((ext_vector_type(8)));
 
 constexpr int G = MIXLLM_GROUP;   // quantization group along K (Sec. 4.1)
 constexpr int TILE_N = 16;        // rows of one packed weight tile

@@ -28,7 +28,7 @@
 //    requests it sets free go out one at a time over the slots behind it.
 //  * Group metadata (4 fp16 scales, 4 zero points) is fetched once per 4 groups.
 //  * Activation scales per (token, group): the products of both scales of a tile come from one
-//    bf16 MFMA, in the accumulators' layout.
+//    fp16 MFMA, in the accumulators' layout.
 //  * Epilogue: token scale (from LDS, where the prologue left the block's), fp16
 //    conversion, scatter to the original channel (Sec. 3.4).
 // 8-bit and 4-bit channel tiles are different block ranges of one launch; where the grid of output
@@ -46,6 +46,9 @@
 namespace mixllm {
 
 constexpr int NSTAGE = 4;   // LDS stages of the activation tile (one group each)
+constexpr int SA_CELL = 8;  // LDS bytes of a (token, group) activation scale: one dword for either half of a wave
+// LDS bytes of `rows` tokens' activation scales: one fp32 number per token, or a cell per token and stage
+constexpr size_t token_scale_bytes(bool per_group, int rows) { return (size_t)rows * (per_group ? NSTAGE * SA_CELL : sizeof(float)); }
 // Launch constants, each settable at build time for measurements (the values are the measured best):
 // groups between the request for packed 4-bit weights and the wait for them, by block shape.  Two
 // and three groups ahead measure within 2 % of each other on every Llama-shaped layer from 64 to
@@ -385,29 +388,22 @@ static __device__ __forceinline__ void prefill_block(const LinearParams &p, int 
         }
 
     // Activation scales per (token, group): s_w[channel] s_a[token] of a 32 x 32 tile is an outer product, and the matrix
-    // pipe, half idle here, forms it in the registers' own layout with one v_mfma_f32_32x32x16_bf16 (a token scale as two
-    // bf16 halves against either half of the channel's: 8 + 3 bits each, so the sum of the four is the exact product of
-    // two fp16 values, the number the multiplication gave).  Sixteen multiplications per tile and group and four wide reads
-    // of the token scales from LDS became one MFMA and one read: the 8B block at 1024 tokens with scales per group on both
-    // sides 516 -> 439 us, K = 4096, N = 28672 at 48 / 256 tokens 28.6 / 66 -> 21.9 / 59.8.
+    // pipe, half idle here, forms it in the registers' own layout with one v_mfma_f32_32x32x16_f16: the two fp16 scales as
+    // they are in the first of the sixteen products, exact in fp32 (subnormal scales included), zeros in the others.  Lanes
+    // 32..63, whose eight products are all of that kind, read a zero for the token and take a zero for the channel, so that
+    // an infinite scale meets the other scale only, and no zero.  Sixteen multiplications per tile and group and four wide
+    // reads of the token scales from LDS became one MFMA and one read: the 8B block at 1024 tokens with scales per group on
+    // both sides 516 -> 439 us, K = 4096, N = 28672 at 48 / 256 tokens 28.6 / 66 -> 21.9 / 59.8, then with either scale as two
+    // bf16 halves (whose products of an infinite scale were all NaN); the fp16 form takes the splitting out, 1024 tokens on
+    // another machine 458 -> 447.
     constexpr bool OUTER = !ACT_PT && DUMP == 0;
     v16f scale_products[NB];   // of the bundle being rescaled
-    auto bf16_halves = [](float f, uint32_t &hi, uint32_t &lo) {   // in the upper half of a dword each
-        hi = __builtin_bit_cast(uint32_t, f) & 0xFFFF0000u;
-        lo = __builtin_bit_cast(uint32_t, f - __builtin_bit_cast(float, hi));
-    };
-    auto token_scale_pair = [&](uint32_t half_bits) -> uint32_t {
-        uint32_t hi, lo;
-        bf16_halves(half_bits_to_float(half_bits), hi, lo);
-        return hi >> 16 | (lo & 0xFFFF0000u);
-    };
-    uint32_t sa_pair[NB];   // this lane's token row of every tile of the bundle (both k slots of 8 hold the same)
-    auto form_products = [&](auto ic, float sw) __attribute__((always_inline)) {
-        uint32_t hi, lo;
-        bf16_halves(sw, hi, lo);
-        const uint32_t d = h ? lo : hi;
-        const v4i a = {(int)sa_pair[decltype(ic)::value], 0, 0, 0}, c = {(int)__builtin_amdgcn_perm(d, d, 0x03020302u), 0, 0, 0};
-        scale_products[decltype(ic)::value] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, c), v16f{}, 0, 0, 0);
+    typedef uint32_t v2u __attribute__((ext_vector_type(2)));   // a token's cell in LDS: its scale's bits, zero
+    uint32_t sa_part[NB];      // this lane's part of the cell, for every tile of the bundle
+    const uint32_t sw_width = h ? 0 : 16;
+    auto form_products = [&](auto ic, uint32_t sw_half) __attribute__((always_inline)) {
+        const v4i a = {(int)sa_part[decltype(ic)::value], 0, 0, 0}, c = {(int)sw_half, 0, 0, 0};
+        scale_products[decltype(ic)::value] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, a), __builtin_bit_cast(v8h, c), v16f{}, 0, 0, 0);
     };
 
     // Rescale (or, for the debug entry point, dump) registers 4j..4j+3 of one finished tile:
@@ -453,7 +449,7 @@ static __device__ __forceinline__ void prefill_block(const LinearParams &p, int 
     // Activation scale (fp16 bits) of (token row tid, group g+1) on its way to LDS: every thread
     // requests one (rows past the tile re-read its last row), so that all waves count the same loads.
     const uint32_t sa_voff = (uint32_t)min(m0 + min(tid, BM - 1), p.M - 1) * (uint32_t)ng * 2u;
-    const uint32_t lds_sa_thread = lds_address(lds_sa) + (uint32_t)min(tid, BM - 1) * (uint32_t)sizeof(float);   // this thread's cell of stage 0
+    const uint32_t lds_sa_thread = lds_address(lds_sa) + (uint32_t)min(tid, BM - 1) * (uint32_t)SA_CELL;   // this thread's cell of stage 0
     if (!ACT_PT && DUMP != 1) {
         load_reg_u16(sa_first, sa_voff, p.xscale + g_lo);
         load_reg_u16(sa_bits, sa_voff, p.xscale + min(g_lo + 1, g_hi - 1));
@@ -484,10 +480,11 @@ static __device__ __forceinline__ void prefill_block(const LinearParams &p, int 
     if constexpr (PART8) await_loads<YOUNGER0>(b[0][0], b[0][1], b[0][2], b[0][3]);
     else await_loads<YOUNGER0>(raw[0][0], raw[0][1]);
     const float sw_row = half_bits_to_float(sw_bits);
+    const uint32_t sw_row_half = __builtin_amdgcn_ubfe(sw_bits, 0, sw_width);
     if (!ACT_PT && DUMP != 1 && tid < BM) {
 #pragma unroll
-        for (int s = 1; s < NSTAGE; ++s) lds_sa[s * BM + tid] = 0.0f;   // read (times a zero scale) before first written
-        ((uint32_t *)lds_sa)[tid] = token_scale_pair(sa_first);
+        for (int s = 1; s < NSTAGE; ++s) ((v2u *)lds_sa)[s * BM + tid] = v2u{0, 0};   // (the scales are read, times zero, before they are first written)
+        ((v2u *)lds_sa)[tid] = v2u{sa_first, 0};
     }
     if constexpr (TOKEN_SCALES)
         if (tid < BM) lds_sa[tid] = half_bits_to_float(ts_bits);
@@ -519,13 +516,14 @@ static __device__ __forceinline__ void prefill_block(const LinearParams &p, int 
 #pragma unroll
         for (int r = 0; r < 16; ++r) scale_products[i][r] = 0.0f;
     typedef __attribute__((address_space(3))) const uint32_t lds_u32;
-    const uint32_t lds_sa_lane = lds_address(lds_sa) + (uint32_t)(mw0 + n32) * 4u;
+    const uint32_t lds_sa_lane = lds_address(lds_sa) + (uint32_t)(mw0 + n32) * (uint32_t)SA_CELL + 4u * (uint32_t)h;
 
     // one group; U = g & 3 selects the register sets and the LDS stage at compile time
     auto group_step = [&](int g, auto uc) {
         constexpr int U = decltype(uc)::value;
-        float sw_cur;
-        if (PART8 && !per_group_s8) sw_cur = g < g_hi ? sw_row : 0.0f;
+        float sw_cur = 0.0f;
+        if constexpr (OUTER) {   // (its bits, in lanes 0..31, are taken where the products are formed)
+        } else if (PART8 && !per_group_s8) sw_cur = g < g_hi ? sw_row : 0.0f;
         else sw_cur = scale_of(meta_cur, U);   // zero for groups past the end (padding)
         int opaque0 = 0;
         if (DUMP == 1) asm volatile("s_mov_b32 %0, 0" : "=s"(opaque0));
@@ -583,8 +581,9 @@ static __device__ __forceinline__ void prefill_block(const LinearParams &p, int 
                     // every thread stores (threads past the tile repeat its last row's value): no
                     // branch in the middle of the group, and a store the compiler does not have to
                     // order against the fragment reads it has in flight
-                    const uint32_t sa_val = token_scale_pair(sa_bits);
-                    asm volatile("ds_write_b32 %0, %1" ::"v"(lds_sa_thread + (uint32_t)(((U + 1) % NSTAGE) * BM * sizeof(float))), "v"(sa_val) : "memory");
+                    // (a group past the end of K: zero, whatever the last group's scale is)
+                    const uint32_t sa_val = sa_bits & keep_next;
+                    asm volatile("ds_write_b32 %0, %1" ::"v"(lds_sa_thread + (uint32_t)(((U + 1) % NSTAGE) * BM * SA_CELL)), "v"(sa_val) : "memory");
                 }
                 mid_group_barrier<(!ACT_PT && DUMP != 1), !C::ALONE>();
                 if constexpr (U == 1) load_meta(g / 4 + 1, meta_nxt);
@@ -608,8 +607,11 @@ static __device__ __forceinline__ void prefill_block(const LinearParams &p, int 
             if constexpr (OUTER) {
                 // the token scales of this bundle are read in its first slots; its products replace those of the bundle
                 // that is rescaled meanwhile, a tile's after its last use
-                if constexpr (j == 0) sa_pair[i] = *(lds_u32 *)(lds_sa_lane + (uint32_t)(((U % NSTAGE) * BM + mt * 32) * 4));
-                if constexpr (j == 3) form_products(std::integral_constant<int, i>{}, sw_cur);
+                if constexpr (j == 0) sa_part[i] = *(lds_u32 *)(lds_sa_lane + (uint32_t)(((U % NSTAGE) * BM + mt * 32) * SA_CELL));
+                if constexpr (j == 3) {
+                    if constexpr (PART8 && !per_group_s8) form_products(std::integral_constant<int, i>{}, g < g_hi ? sw_row_half : 0u);
+                    else form_products(std::integral_constant<int, i>{}, __builtin_amdgcn_ubfe(U & 2 ? meta_cur.s.y : meta_cur.s.x, U & 1 ? 16 : 0, sw_width));
+                }
             }
             // the requests of this group: weights (4-bit tiles), then activations
             if constexpr (!AT_BARRIER && st >= HALF) {
@@ -945,7 +947,7 @@ __global__ __launch_bounds__(C::THREADS, MINW) void linear_prefill_kernel(Linear
 constexpr int SLICES = 4;
 constexpr size_t slices_lds_bytes(bool act_pt)
 {
-    return (size_t)SLICES * (NSTAGE * 32 * G + (act_pt ? 1 : NSTAGE) * 32 * sizeof(float));   // two blocks fit a CU
+    return (size_t)SLICES * (NSTAGE * 32 * G + token_scale_bytes(!act_pt, 32));   // two blocks fit a CU
 }
 template <bool ACT_PT, bool W8PC>
 __global__ __launch_bounds__(64 * SLICES, 2) void linear_slices_kernel(LinearParams p, int nbm, int nb8, int nb4, int per4, int per8)
@@ -962,7 +964,7 @@ __global__ __launch_bounds__(64 * SLICES, 2) void linear_slices_kernel(LinearPar
     const int quads = (p.ng + 3) / 4;
     const int g_lo = slice * quads / SLICES * 4, g_hi = min(p.ng, (slice + 1) * quads / SLICES * 4);   // (never empty: quads >= SLICES)
     uint8_t *lds_a = smem + slice * NSTAGE * C::A_STAGE;
-    float *lds_sa = (float *)(smem + SLICES * NSTAGE * C::A_STAGE) + slice * (ACT_PT ? 1 : NSTAGE) * C::BM;
+    float *lds_sa = (float *)(smem + SLICES * NSTAGE * C::A_STAGE + slice * token_scale_bytes(!ACT_PT, C::BM));
     if (part8) {
         if constexpr (W8PC && ACT_PT)
             prefill_block_w8_channel_scale<C, ACT_PT, 0>(p, bm * C::BM, bn * 2, g_lo, g_hi, 0, lds_a, lds_sa, smem);
@@ -1021,7 +1023,7 @@ template <typename C, typename K>
 static int launch_variant(K kernel, bool with_sa, dim3 grid, dim3 block, hipStream_t st, const LinearParams &p, int nbm4,
                           int nbm8, int nb8, int nb4, int per4, int per8, int band4, int band8, int half8)
 {
-    const size_t lds_bytes = (size_t)NSTAGE * C::A_STAGE + (with_sa ? (size_t)NSTAGE : 1) * C::BM * sizeof(float);
+    const size_t lds_bytes = (size_t)NSTAGE * C::A_STAGE + token_scale_bytes(with_sa, C::BM);
     // (kernel, device) pairs already configured; a handful of instantiations exist
     struct Done {
         const void *fn;
@@ -1294,7 +1296,7 @@ bool prefill_plan(const LinearParams &p, int out[13])
     out[4] = g.nb4;
     out[5] = (g.per4 + g.per8) * 8;
     out[6] = g.band4;
-    out[7] = NSTAGE * BM * G + ((!p.act_per_token && !p.P) ? NSTAGE : 1) * BM * (int)sizeof(float);   // (p.P is never set here)
+    out[7] = NSTAGE * BM * G + (int)token_scale_bytes(!p.act_per_token && !p.P, BM);   // (p.P is never set here)
     int qpp;
     out[8] = choose_kparts(p, tm, ~(size_t)0, qpp);   // blocks sharing a K range when the caller brings the scratch for it
     out[9] = 4 * qpp;                                 // quantization groups per part

@@ -12,7 +12,7 @@ from oracle import ref
 from paper_2412_14590_amd import synth
 
 from util import (G, TOL, check_against_oracle, dev, full_size_layer, make_case, pack_from_oracle, row_rel_err,
-                  stratified_rows)
+                  stratified_rows, weight_scales_in_channel_order)
 
 pytestmark = pytest.mark.gpu
 
@@ -676,6 +676,44 @@ def test_outputs_beyond_the_fp16_range_become_infinities(M):
         assert np.array_equal(np.sign(y[np.isinf(y)]), np.sign(y_ref[np.isinf(y_ref)]))
         fin = np.isfinite(y_ref)
         assert np.allclose(y[fin].astype(np.float64), y_ref[fin].astype(np.float64), rtol=2e-3)
+
+
+@pytest.mark.parametrize("subnormal", ["token", "channel"])
+@pytest.mark.parametrize("M,K,path", [(40, 2048, "auto"), (33, 640, "prefill32"), (70, 2048, "prefill64")])
+def test_subnormal_scales_per_group_are_not_flushed(M, K, path, subnormal):
+    # ... by the matrix pipe, which multiplies them: scales of a few 2^-24 on one side, large ones on the other
+    N, n8 = 70, 20
+    _, _, L, _, xq, xs = make_case(M, K, N, n8, seed=44, w8_group=128, act_group=128)
+    rng = np.random.default_rng(44)
+    for a, side in ((xs, "token"), (L.s4, "channel"), (L.s8, "channel")):
+        a[:] = rng.integers(1, 1024, a.shape) * 2.0 ** -24 if side == subnormal else rng.uniform(1.0, 8.0, a.shape)
+    y = mx.mixed_linear(dev(xq), dev(xs), pack_from_oracle(L), mx.PATH_AUTO if path == "auto" else PATHS[path])
+    check_against_oracle(y.cpu().numpy(), xq, xs, L, ("subnormal", subnormal, M, K, path))
+
+
+@pytest.mark.parametrize("w8_group", [None, 128])
+@pytest.mark.parametrize("M,K,path", [(40, 2048, "auto"), (40, 1664, "auto"), (33, 640, "prefill32"), (33, 2048, "prefill32"), (70, 640, "prefill64"), (70, 2048, "prefill64"),
+                                      (150, 1152, "auto")])
+def test_infinite_and_nan_scales_per_group_reach_the_outputs_they_belong_to(M, K, path, w8_group):
+    # scales per (token, group) are multiplied by the matrix pipe from bf16 halves: an infinite scale of a token or of a
+    # channel gives the infinities, and the NaNs, of the sum of P s_w s_a, on its row or column only - the last
+    # group of a K that ends inside a group of four included
+    N, n8, ng = 70, 20, K // 128
+    _, _, L, x, xq, xs = make_case(M, K, N, n8, seed=43, w8_group=w8_group, act_group=128)
+    inf, nan = np.float16(np.inf), np.float16(np.nan)
+    xs[0, 0], xs[1, ng - 1], xs[2, 2], xs[3, 1], xs[4, :2], xs[5, 0], xs[M - 1, ng // 2] = inf, inf, nan, -inf, inf, 0, inf
+    L.s4[7, 1], L.s4[8, ng - 1], L.s8[3, 0], L.s8[4, -1], L.s4[9, 0], L.s4[30, 0] = inf, -inf, inf, nan, nan, 0
+    with np.errstate(all="ignore"):
+        sw = weight_scales_in_channel_order(L)
+        y64 = (ref.group_partials(xq, L).astype(np.float64) * (sw[None] * xs.astype(np.float64)[:, None, :])).sum(axis=2)
+        want = y64.astype(np.float16)
+    assert np.isinf(want).any() and np.isnan(want).any() and np.isfinite(want[6:]).mean() > 0.8
+    y = mx.mixed_linear(dev(xq), dev(xs), pack_from_oracle(L), mx.PATH_AUTO if path == "auto" else PATHS[path]).cpu().numpy()
+    assert np.array_equal(np.isnan(y), np.isnan(want)) and np.array_equal(np.isinf(y), np.isinf(want))
+    assert np.array_equal(y[np.isinf(want)], want[np.isinf(want)])
+    fin = np.isfinite(want)
+    rms = np.sqrt(np.mean(want[fin].astype(np.float64) ** 2))
+    assert np.abs(y[fin].astype(np.float64) - y64[fin]).max() <= 1e-3 * max(rms, np.abs(y64[fin]).max())
 
 
 def test_random_shapes_through_every_path_that_covers_them():
