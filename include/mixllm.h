@@ -76,6 +76,10 @@ enum {
     MIXLLM_PATH_PREFILL_128 = 10     /* EUNSUPPORTED with one activation scale per (token, group) */
 };
 
+/* What mixllm_debug_work_split reports where MIXLLM_PATH_AUTO takes the tiles of 32 x 32 cut along K over the waves of
+ * a block; not a value of `path`. */
+enum { MIXLLM_PLAN_SLICES = 100 };
+
 typedef struct mixllm_desc {
     int32_t M;         /* tokens (rows of x and y); may be 0 for the offline calls */
     int32_t K;         /* input features, multiple of 128, at most MIXLLM_MAX_K */
@@ -305,8 +309,11 @@ int mixllm_debug_check_fast_division(uint64_t *mismatches, void *stream);
  * tiles of the 8-bit and of the 4-bit part, blocks launched per K part, token tiles per band of the
  * block order (4-bit part), bytes of LDS, K parts (with linear_workspace_bytes of scratch),
  * quantization groups per K part, then token rows of a block tile of the 8-bit part (the 4-bit
- * part's, or half of that in a short launch of 128-row tiles), its token tiles and its token tiles per band.  plan must hold
- * 16 ints.  Returns EUNSUPPORTED when the path does not cover the shape, EINVAL for other
+ * part's, or half of that in a short launch of 128-row tiles), its token tiles and its token tiles per band;
+ * path = MIXLLM_PATH_AUTO: plan[0..1] = the kernel the library takes for the linear without scratch and with
+ * linear_workspace_bytes of it (a MIXLLM_PATH value, or MIXLLM_PLAN_SLICES), plan[2..7] = the launch of the tiles cut
+ * along K for this shape, taken or not: token tiles, channel tiles of the 8-bit and of the 4-bit part, blocks
+ * launched, waves of a block (slices of K), bytes of LDS.  plan must hold 16 ints.  Returns EUNSUPPORTED when the path does not cover the shape, EINVAL for other
  * paths.
  */
 int mixllm_debug_work_split(const mixllm_desc *d, int path, int32_t *plan);

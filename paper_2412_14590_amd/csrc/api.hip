@@ -152,7 +152,7 @@ namespace {
 int hip_status(int e) { return e == (int)hipSuccess ? MIXLLM_OK : MIXLLM_EHIP; }
 
 // the tiles cut along K over the waves of a block: taken by the library's choice only
-constexpr int PATH_SLICES = 100;
+constexpr int PATH_SLICES = MIXLLM_PLAN_SLICES;
 
 // The library's choice of kernel.  Up to 16 tokens the decode path.  17 to 64 tokens lie between the
 // two paths the workload names.  Measured with every launch reading its weights from HBM (copies of
@@ -534,6 +534,15 @@ int mixllm_debug_work_split(const mixllm_desc *d, int path, int32_t *plan)
     if (path == MIXLLM_PATH_DECODE_SPLIT) ok = decode_split_plan(p, out);
     else if (path == MIXLLM_PATH_MID) ok = mid_plan(p, out);
     else if (path == MIXLLM_PATH_PREFILL) ok = prefill_plan(p, out);
+    else if (path == MIXLLM_PATH_AUTO) {
+        LinearParams with_scratch = p;
+        with_scratch.partials_cap = prefill_scratch_bytes(p);
+        if (with_scratch.partials_cap) with_scratch.partials = (float *)16;   // (only its presence is looked at)
+        out[0] = auto_path(*d, p);
+        out[1] = auto_path(*d, with_scratch);
+        slices_plan(p, out + 2);
+        ok = true;
+    }
     else return MIXLLM_EINVAL;
     if (!ok) return MIXLLM_EUNSUPPORTED;
     for (int i = 0; i < 16; ++i) plan[i] = out[i];

@@ -234,6 +234,7 @@ bool prefill_covers(const LinearParams &p);
 // tiles cut along K over the waves of a block (linear_prefill.hip): where they pay, and the launch
 bool slices_pay(const LinearParams &p);
 int launch_linear_slices(const LinearParams &p, hipStream_t st);
+void slices_plan(const LinearParams &p, int out[6]);
 // scratch bytes the tiled kernel would like for `p` (0 where it does not split K)
 size_t prefill_scratch_bytes(const LinearParams &p);
 // true when the tiled kernel, given p.partials / p.partials_cap, would split K for `p`

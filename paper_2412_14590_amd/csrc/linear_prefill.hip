@@ -1246,6 +1246,22 @@ int launch_linear_prefill(const LinearParams &p0, hipStream_t st)
     }
 }
 
+// the grid of linear_slices_kernel: token tiles, channel tiles of either part, blocks per XCD of either part
+struct SlicesGrid {
+    int nbm, nb8, nb4, per4, per8;
+    int blocks() const { return (per4 + per8) * 8; }
+};
+static SlicesGrid slices_grid(const LinearParams &p)
+{
+    SlicesGrid g;
+    g.nbm = (p.M + 31) / 32;
+    g.nb8 = (p.ntiles8 + 1) / 2;
+    g.nb4 = (p.ntiles4 + 1) / 2;
+    g.per4 = (g.nbm * g.nb4 + 7) / 8;
+    g.per8 = (g.nbm * g.nb8 + 7) / 8;
+    return g;
+}
+
 // Where linear_slices_kernel takes over.  It needs a group of 4 quantization groups for each of its waves, and pays while
 // all its blocks run at once, two to a CU (K = N = 4096 at 128 tokens, 520 blocks: 12.5 us against 13.7; N = 6144 at 96, 582
 // blocks: 14.7 against 14.0; at 128, 776 blocks: 15.6 against 14.1).  A long K is a long chain again: with two blocks on a
@@ -1267,16 +1283,27 @@ bool slices_pay(const LinearParams &p)
 int launch_linear_slices(const LinearParams &p, hipStream_t st)
 {
     if (p.M == 0 || p.N == 0) return hipSuccess;
-    const int nbm = (p.M + 31) / 32, nb8 = (p.ntiles8 + 1) / 2, nb4 = (p.ntiles4 + 1) / 2;
-    const int per4 = (nbm * nb4 + 7) / 8, per8 = (nbm * nb8 + 7) / 8;
+    const SlicesGrid g = slices_grid(p);
     auto go = [&](auto kernel, bool act_pt) {
         const size_t lds = slices_lds_bytes(act_pt);
         if (int e = ensure_dynamic_lds((const void *)kernel, lds)) return e;
-        hipLaunchKernelGGL(kernel, dim3((per4 + per8) * 8), dim3(64 * SLICES), lds, st, p, nbm, nb8, nb4, per4, per8);
+        hipLaunchKernelGGL(kernel, dim3(g.blocks()), dim3(64 * SLICES), lds, st, p, g.nbm, g.nb8, g.nb4, g.per4, g.per8);
         return (int)hipGetLastError();
     };
     if (p.act_per_token) return p.w8_per_channel ? go(linear_slices_kernel<true, true>, true) : go(linear_slices_kernel<true, false>, true);
     return p.w8_per_channel ? go(linear_slices_kernel<false, true>, false) : go(linear_slices_kernel<false, false>, false);
+}
+
+// the launch plan as six integers (token tiles, channel tiles of either part, blocks, slices, bytes of LDS)
+void slices_plan(const LinearParams &p, int out[6])
+{
+    const SlicesGrid g = slices_grid(p);
+    out[0] = g.nbm;
+    out[1] = g.nb8;
+    out[2] = g.nb4;
+    out[3] = g.blocks();
+    out[4] = SLICES;
+    out[5] = (int)slices_lds_bytes(p.act_per_token);
 }
 
 // the launch plan as thirteen integers (token rows and channels of a block tile of the 4-bit part, its

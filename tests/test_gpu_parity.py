@@ -481,6 +481,43 @@ def test_tiles_cut_along_k_over_the_waves_of_a_block(M, K, N, n8, variant):
     assert torch.equal(y, mx.linear_fp16(dev(x), PL, act_group=ag))
 
 
+def library_choice(M, K, N, n8, act_group=None, w8_group=None):
+    """The kernel MIXLLM_PATH_AUTO takes: (without scratch, with the scratch the library asks for)."""
+    import ctypes as C
+    from paper_2412_14590_amd import binding
+    out = (C.c_int32 * 16)()
+    d = binding._desc(M, K, N, n8, act_group, w8_group)
+    assert mx.lib().mixllm_debug_work_split(C.byref(d), mx.PATH_AUTO, C.cast(out, C.c_void_p)) == 0
+    return out[0], out[1]
+
+
+SLICES = 100   # MIXLLM_PLAN_SLICES
+
+
+@pytest.mark.parametrize("act_group", [None, 128])
+@pytest.mark.parametrize("w8_group", [None, 128])
+@pytest.mark.parametrize("M,K,N,n8", [(17, 1664, 16, 3), (33, 1920, 75, 33), (64, 4224, 64, 0), (40, 4096, 530, 530),
+                                     (130, 2048, 1000, 100), (64, 8192, 257, 26)])
+def test_tiles_cut_along_k_add_up_the_integer_sums(M, K, N, n8, w8_group, act_group):
+    # The kernel has no debug variant that hands out its integers: scales of 1 and 2, different from group to group and
+    # small codes make the outputs the integers themselves (every sum exact in fp32, converted to fp16 once).  Slices of
+    # uneven length, a last slice with groups past the end of K, both parts, ragged tiles of tokens and channels.
+    assert library_choice(M, K, N, n8, act_group, w8_group)[0] == SLICES
+    rng = np.random.default_rng(M + K)
+    ng, n4 = K // 128, N - n8
+    L = make_case(0, K, N, n8, seed=45, w8_group=w8_group)[2]
+    if n8:
+        L.q8[:], L.s8[:] = rng.integers(-8, 9, L.q8.shape), rng.integers(1, 3, L.s8.shape)
+    if n4:
+        L.q4[:], L.z4[:], L.s4[:] = rng.integers(0, 16, L.q4.shape), rng.integers(0, 16, L.z4.shape), rng.integers(1, 3, L.s4.shape)
+    xq = (rng.integers(-1, 2, (M, K)) * (rng.random((M, K)) < 0.25)).astype(np.int8)
+    xs = rng.integers(1, 3, (M, 1 if act_group is None else ng)).astype(np.float16)
+    y64 = (ref.group_partials(xq, L).astype(np.float64) * (weight_scales_in_channel_order(L)[None] * xs.astype(np.float64)[:, None, :])).sum(axis=2)
+    assert np.abs(y64).max() < 65504 and (np.abs(y64) <= 2048).mean() > 0.99      # integers fp16 holds, nearly all
+    y = mx.mixed_linear(dev(xq), dev(xs), pack_from_oracle(L)).cpu().numpy()
+    assert np.array_equal(y, y64.astype(np.float16))
+
+
 @pytest.mark.parametrize("M,K,N,n8", [(17, 256, 7, 2), (33, 384, 70, 70), (64, 1024, 530, 0), (50, 640, 50, 5),
                                      (64, 512, 300, 30), (20, 4096, 1000, 100), (64, 14336, 272, 27), (1, 512, 96, 9),
                                      (48, 2048, 2070, 207)])
@@ -770,7 +807,8 @@ def check_cell(lay, L, PL, M, seed, act_group=None):
     """One (layer, M) cell of a workload at full size, through the call the benchmark times
     (mixllm_mixed_linear_fp16, library's choice of kernel).
     Up to 64 tokens: every row against the oracle (row norm and per element), codes, scales and the
-    per-group partials of the dispatched kernel bit-exact.
+    per-group partials bit-exact - of the kernel the library takes for them, which is the linear's own except where
+    that is the tiles cut along K: their sums have a test of their own.
     More tokens (the oracle is O(MNK)): a stratified sample of rows against the oracle the same way
     (one row per 32-token tile, first and last row of every 128-token block), and ALL rows against
     the one-thread-per-output kernel on the GPU, which the sample pins to the oracle: the int32 sums

@@ -230,3 +230,45 @@ def test_prefill_block_tile_follows_the_grid_size():
     assert check_prefill_grid(2048, 4096, 4096, 410) == 128
     assert check_prefill_grid(128, 4096, 28672, 2867) == 128
     assert check_prefill_grid(2048, 4096, 28672, 2867, act_group=128) == 64
+
+
+SLICES = 100   # MIXLLM_PLAN_SLICES
+
+
+def auto_plan(M, K, N, n8, act_group=None, w8_group=None):
+    out = (C.c_int32 * 16)()
+    d = binding._desc(M, K, N, n8, act_group, w8_group)
+    assert mx.lib().mixllm_debug_work_split(C.byref(d), mx.PATH_AUTO, C.cast(out, C.c_void_p)) == 0
+    return list(out)
+
+
+@pytest.mark.parametrize("M,K,N,n8", [(17, 1664, 16, 3), (33, 1920, 70, 0), (65, 4224, 64, 64), (300, 4096, 257, 26), (64, 8192, 1000, 100),
+                                     (40, 14336, 4095, 409), (48, 28672, 8448, 0), (1000, 2048, 530, 53)])
+@pytest.mark.parametrize("act_group", [None, 128])
+def test_tiles_cut_along_k_cover_every_tile_and_group_once(M, K, N, n8, act_group):
+    # linear_prefill.hip, linear_slices_kernel: its block -> tile mapping and its slices of K restated
+    nbm, nb8, nb4, blocks, slices, lds = auto_plan(M, K, N, n8, act_group)[2:8]
+    t8, t4 = tiles(N, n8)
+    assert nbm == -(-M // 32) and nb8 == -(-t8 // 2) and nb4 == -(-t4 // 2) and lds <= 80 * 1024
+    per4, per8 = -(-nbm * nb4 // 8), -(-nbm * nb8 // 8)
+    assert blocks == 8 * (per4 + per8)
+    seen = set()
+    for b in range(blocks):
+        xcd, i = b & 7, b >> 3
+        part8 = i >= per4
+        nb, L = (nb8, xcd * per8 + i - per4) if part8 else (nb4, xcd * per4 + i)
+        if L < nbm * nb:
+            seen.add((part8, L - L // nbm * nbm, L // nbm))
+    assert seen == {(p, m, n) for p, nb in ((False, nb4), (True, nb8)) for m in range(nbm) for n in range(nb)}
+    ng = K // 128
+    quads = (ng + 3) // 4
+    bounds = [(s * quads // slices * 4, min(ng, (s + 1) * quads // slices * 4)) for s in range(slices)]
+    assert bounds[0][0] == 0 and bounds[-1][1] == ng and all(a < b for a, b in bounds)        # no wave without a group
+    assert all(bounds[s][1] == bounds[s + 1][0] and bounds[s][1] % 4 == 0 for s in range(slices - 1))
+
+
+def test_library_choice_up_to_sixteen_tokens_and_on_short_k():
+    assert auto_plan(16, 4096, 4096, 410)[:2] == [mx.PATH_DECODE] * 2
+    assert auto_plan(17, 1536, 1000, 100)[:2] == [mx.PATH_MID] * 2            # 12 groups: a wave would have none
+    assert auto_plan(17, 1664, 1000, 100)[:2] == [SLICES] * 2
+    assert auto_plan(300, 1536, 1000, 100)[:2] == [mx.PATH_PREFILL] * 2
