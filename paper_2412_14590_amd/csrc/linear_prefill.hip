@@ -1262,22 +1262,45 @@ static SlicesGrid slices_grid(const LinearParams &p)
     return g;
 }
 
-// Where linear_slices_kernel takes over.  It needs a group of 4 quantization groups for each of its waves, and pays while
-// all its blocks run at once, two to a CU (K = N = 4096 at 128 tokens, 520 blocks: 12.5 us against 13.7; N = 6144 at 96, 582
-// blocks: 14.7 against 14.0; at 128, 776 blocks: 15.6 against 14.1).  A long K is a long chain again: with two blocks on a
-// CU the line lies at K = 8192 (64 tokens, N = 8192: 21.7 against 25.2; K = 14336, N = 4096 at 100 tokens 30 against 24.7, K
-// split over blocks), with one at K = 14336 (N = 4096 at 20 tokens 17.8 against 19.4; N = 1000 at 130 13.4 against 17.8;
-// K = 28672, N = 2000 at 60 tokens 31 against 27).  With one token tile the path for a few dozen tokens reads the weights
-// evenly, and where CUs would get a second block it is level or ahead (32 tokens, N = 8192, 258 blocks: 11.4 against 12.2 at K =
-// 4096, 18.2 against 19.8 at K = 8192).  Up to 16 tokens the decode kernels are ahead (K = N = 4096: 7.2 against
-// 7.8).  Beyond 64 tokens a call that brings the scratch to split K over blocks gets that split, and with it the same sums
-// as from the tiled path by name.
+// Where linear_slices_kernel takes over: from 17 tokens (up to 16 the decode kernels are ahead, K = N = 4096: 7.2 us
+// against 7.8), with a group of 4 quantization groups or more for each of its waves, while all its blocks run at once.
+// The lines lie where the two sides change places, measured in turn on one machine with every launch's weights from HBM
+// and 10 % 8-bit channels: 5900 pairs, 17 to 400 tokens, K = 1664 .. 28672, both granularities of the activation scales
+// ("grouped" = one per token and group).  A factor is the time of the kernel that otherwise takes the call over the slices'.
+//  * One block a CU.  What counts is the busiest XCD: 256 tiles make 264 blocks in eight equal ranges of either part, and the
+//    second block on some CUs costs 30 % (K = 4096 at 17 tokens: 8.1 us with 248 blocks, 10.9 with 264).  Factor 1.2 to 3.7
+//    at any K where the other side does not split K over blocks (up to 32 tokens it does beyond K = 8192).  Against a split,
+//    K = 8192 0.93 to 1.7, grouped 0.83 to 1.33; otherwise from 7/16 of the CUs on: grouped 0.91 to 1.4, else 0.95 to 1.5, below
+//    that 0.64 to 1.2 (K = 14336 at 17 / 32 tokens: 120 blocks 1.12 / 1.01, 104 blocks 0.90 / 0.78).  Never at K = 28672
+//    (0.43 to 1.27).  (Two places where the split is ahead stay with the slices, because calls there give the same bits with
+//    scratch and without: grouped, K = 8192, fewer than 96 blocks, 33 to 64 tokens, and, beyond K = 8192, up to 24
+//    tokens and three blocks an XCD, 0.68 to 1.05.)
+//  * Two blocks a CU, one token tile: the path for a few dozen tokens reads the weights evenly and is level or ahead
+//    (K = 8192, 264 to 392 blocks: 0.97 to 1.00 at 17 tokens, 0.89 to 0.95 at 32) until its blocks hold more virtual tiles than
+//    a CU has SIMDs: more weights than four 4-bit tiles a CU (K = 8192, 472 blocks 1.08 / 1.02, 480 blocks 1.37 / 1.26; K = 2048
+//    1.15 / 1.12).  Grouped, up to 24 tokens and K = 8192, 0.98 to 1.14 before that as well (at 32 tokens 0.92 to 1.04).
+//  * Two blocks a CU, more tokens: 1.02 to 2.4.  Against a split 0.96 to 1.4 at K = 8192, grouped from 3/2 blocks a CU on
+//    (1.01 to 1.29, 296 blocks 0.87 to 0.95); beyond that K 0.60 to 1.2.
+//  * A few blocks more than two a CU, which run by themselves at the end: from K = 4096 on, one more an XCD (0.99 to 1.19), two
+//    from 65 tokens on or grouped (1.03 to 1.42; else 0.85 to 1.15).  Shorter K 0.85 to 1.0; one token tile 0.79 to 1.16.
+// Beyond 64 tokens a call that brings the scratch to split K over blocks gets that split although the slices are ahead at
+// K = 8192 (0.87 to 1.7): its results are those of the tiled path by name, bit for bit, which is kept.
 bool slices_pay(const LinearParams &p)
 {
     if (p.P || p.S || p.M <= 16 || p.ng < 4 * SLICES - 3 || !prefill_covers(p)) return false;
-    if (p.M > 64 && prefill_would_split(p)) return false;
-    const long blocks = (long)((p.M + 31) / 32) * ((p.ntiles8 + 1) / 2 + (p.ntiles4 + 1) / 2), cus = cu_count();
-    return blocks <= cus ? p.ng <= 112 : p.M > 32 && blocks <= 2 * cus + cus / 16 && p.ng <= 64;
+    const bool split = prefill_would_split(p), grouped = !p.act_per_token;
+    if (p.M > 64 && split) return false;
+    const long blocks = slices_grid(p).blocks(), cus = cu_count();
+    if (blocks <= cus) {
+        if (!split || p.ng <= 64) return true;
+        return p.ng <= 112 && (16 * blocks > 7 * cus || (p.M <= 24 && blocks <= 24));
+    }
+    if (split && (p.ng > 64 || (grouped && p.M > 32 && 2 * blocks < 3 * cus))) return false;
+    if (p.M <= 32) {
+        const bool many_tiles = p.ntiles4 > 0 && p.ntiles4 + 2L * p.ntiles8 > 4 * cus;
+        return blocks <= 2 * cus && (many_tiles || (grouped && p.M <= 24 && p.ng <= 64));
+    }
+    return blocks <= 2 * cus + (p.ng < 32 ? 0 : p.M <= 64 && !grouped ? 8 : 16);
 }
 
 int launch_linear_slices(const LinearParams &p, hipStream_t st)

@@ -497,7 +497,8 @@ SLICES = 100   # MIXLLM_PLAN_SLICES
 @pytest.mark.parametrize("act_group", [None, 128])
 @pytest.mark.parametrize("w8_group", [None, 128])
 @pytest.mark.parametrize("M,K,N,n8", [(17, 1664, 16, 3), (33, 1920, 75, 33), (64, 4224, 64, 0), (40, 4096, 530, 530),
-                                     (130, 2048, 1000, 100), (64, 8192, 257, 26)])
+                                     (130, 2048, 1000, 100), (64, 8192, 257, 26),
+                                     (17, 1664, 7936, 31), (32, 1664, 15488, 1549), (48, 2048, 8000, 800), (48, 4096, 8192, 819)])   # full grids of one and two blocks a CU
 def test_tiles_cut_along_k_add_up_the_integer_sums(M, K, N, n8, w8_group, act_group):
     # The kernel has no debug variant that hands out its integers: scales of 1 and 2, different from group to group and
     # small codes make the outputs the integers themselves (every sum exact in fp32, converted to fp16 once).  Slices of
@@ -516,6 +517,16 @@ def test_tiles_cut_along_k_add_up_the_integer_sums(M, K, N, n8, w8_group, act_gr
     assert np.abs(y64).max() < 65504 and (np.abs(y64) <= 2048).mean() > 0.99      # integers fp16 holds, nearly all
     y = mx.mixed_linear(dev(xq), dev(xs), pack_from_oracle(L)).cpu().numpy()
     assert np.array_equal(y, y64.astype(np.float16))
+
+
+@pytest.mark.parametrize("variant", ["baseline", "paper"])
+@pytest.mark.parametrize("M,K,N,n8", [(40, 28672, 300, 30), (130, 16512, 530, 53), (17, 131072, 40, 20)])
+def test_tiles_cut_along_k_on_long_k_without_scratch(M, K, N, n8, variant):
+    ag, wg = {"baseline": (None, None), "paper": (128, 128)}[variant]
+    assert library_choice(M, K, N, n8, ag, wg) == (SLICES, mx.PATH_PREFILL)
+    _, _, L, x, xq, xs = make_case(M, K, N, n8, seed=46, w8_group=wg, act_group=ag)
+    y = mx.mixed_linear(dev(xq), dev(xs), pack_from_oracle(L))
+    check_against_oracle(y.cpu().numpy(), xq, xs, L, ("slices, long K", variant, M, K, N, n8))
 
 
 @pytest.mark.parametrize("M,K,N,n8", [(17, 256, 7, 2), (33, 384, 70, 70), (64, 1024, 530, 0), (50, 640, 50, 5),

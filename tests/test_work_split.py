@@ -272,3 +272,40 @@ def test_library_choice_up_to_sixteen_tokens_and_on_short_k():
     assert auto_plan(17, 1536, 1000, 100)[:2] == [mx.PATH_MID] * 2            # 12 groups: a wave would have none
     assert auto_plan(17, 1664, 1000, 100)[:2] == [SLICES] * 2
     assert auto_plan(300, 1536, 1000, 100)[:2] == [mx.PATH_PREFILL] * 2
+
+
+# (M, K, N, n8, grouped activation scales, taken without scratch, taken with it): on either side of every line of the rule, on a
+# 256-CU part (the fallback count without a GPU is also 256)
+CHOICE = [
+    (17, 4096, 7936, 794, False, True, True), (17, 4096, 8192, 819, False, False, False),      # 248 blocks; 257 tiles are 264
+    (32, 4096, 8192, 819, True, False, False), (24, 4096, 8192, 819, True, True, True), (25, 4096, 8192, 819, True, False, False),
+    (24, 11008, 8192, 819, True, False, False), (24, 14336, 8160, 816, True, False, False),
+    (17, 4096, 14816, 1482, False, False, False), (32, 4096, 15360, 1536, False, True, True),  # more than four 4-bit tiles a CU
+    (17, 4096, 16384, 1638, False, False, False),                                              # more than two blocks a CU
+    (17, 4096, 8400, 8400, False, False, False),                                               # 8-bit tiles only
+    (17, 14336, 15360, 1536, False, True, False),
+    (40, 14336, 4095, 409, False, True, False), (20, 28672, 6400, 640, False, True, False),
+    (20, 14336, 3000, 300, False, True, False), (20, 14336, 3700, 370, False, True, True),     # 7/16 of the CUs
+    (20, 14336, 3000, 300, True, True, False), (20, 14336, 3700, 370, True, True, True),
+    (17, 14336, 500, 50, True, True, True), (17, 14336, 700, 70, False, True, False), (25, 14336, 500, 50, True, True, False),
+    (48, 8192, 800, 80, True, True, True), (48, 8192, 800, 80, False, True, True),
+    (48, 4096, 4096, 410, False, True, True), (64, 8192, 4576, 458, False, True, True), (64, 8192, 4576, 458, True, True, False),
+    (64, 8192, 6624, 662, True, True, True), (64, 11008, 4576, 458, False, True, False),
+    (64, 8192, 8192, 819, False, True, True), (64, 8192, 8320, 832, False, False, False), (64, 8192, 8320, 832, True, True, True),
+    (48, 2048, 8000, 800, False, True, True), (48, 2048, 8192, 819, False, False, False),
+    (128, 4096, 4096, 410, False, True, True), (96, 4096, 6144, 614, False, False, False), (130, 8192, 1030, 103, False, True, False),
+]
+
+
+@pytest.mark.parametrize("M,K,N,n8,grouped,alone,scratch", CHOICE)
+def test_lines_of_the_tiles_cut_along_k(M, K, N, n8, grouped, alone, scratch):
+    p = auto_plan(M, K, N, n8, 128 if grouped else None)
+    assert [p[0] == SLICES, p[1] == SLICES] == [alone, scratch], p
+
+
+def test_shapes_the_gpu_tests_of_the_tiles_cut_along_k_count_on():
+    # test_gpu_parity.py, test_tiles_cut_along_k_over_the_waves_of_a_block: its two shapes past a line take another kernel
+    for M, K, N, n8, taken in [(17, 1664, 16, 3, 1), (32, 1664, 33, 33, 1), (33, 1920, 70, 0, 1), (65, 4224, 64, 6, 1), (17, 14336, 300, 30, 1),
+                               (300, 4096, 257, 26, 1), (64, 8192, 1000, 100, 1), (40, 1920, 4095, 409, 1), (32, 2048, 8160, 31, 0),
+                               (32, 2048, 8192, 31, 0), (48, 2048, 8448, 0, 0), (48, 2048, 8449, 0, 0)]:
+        assert (auto_plan(M, K, N, n8)[0] == SLICES) == bool(taken), (M, K, N, n8)
