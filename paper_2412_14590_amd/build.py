@@ -208,9 +208,10 @@ def build(force: bool = True, verbose: bool = False) -> str:
                     os.remove(stale)
             raise
     subprocess.run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], check=True)
+    if not variant or not os.path.exists(CALLS):   # (host code: the same for every variant)
+        build_calls()
     if variant:
         return LIB
-    build_calls()
     # the ceiling probes of the benchmark: a separate small library
     r = subprocess.run([_hipcc(), *FLAGS, "-shared", "-o", PROBE_LIB, os.path.join(CSRC, "probe.hip")],
                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)

@@ -287,3 +287,16 @@ def test_static_entry_and_debug_hooks_refuse_activations_of_another_width():
             with pytest.raises(AssertionError) as e:
                 call()
             assert "device" not in str(e.value)        # refused for its width, before any address is taken
+
+
+def test_a_variant_build_brings_the_native_calls_where_there_are_none(tmp_path, monkeypatch):
+    # a library with other launch constants is loaded by the same package, which needs _calls.so beside it
+    from paper_2412_14590_amd import build
+    calls, made = tmp_path / "_calls.so", []
+    monkeypatch.setenv("MIXLLM_EXTRA_FLAGS", "-DX=1")
+    for name, value in (("SOURCES", []), ("NO_SPILL", {}), ("LIB", str(tmp_path / "lib.so")), ("CALLS", str(calls)),
+                        ("_hipcc", lambda: "true"), ("build_calls", lambda: (made.append(1), calls.write_text("")))):
+        monkeypatch.setattr(build, name, value)
+    build.build()
+    build.build()
+    assert made == [1]
