@@ -154,18 +154,19 @@ int hip_status(int e) { return e == (int)hipSuccess ? MIXLLM_OK : MIXLLM_EHIP; }
 // the tiles cut along K over the waves of a block: taken by the library's choice only
 constexpr int PATH_SLICES = MIXLLM_PLAN_SLICES;
 
-// The library's choice of kernel.  Up to 16 tokens the decode path.  17 to 64 tokens lie between the
-// two paths the workload names.  Measured with every launch reading its weights from HBM (copies of
-// the layer rotating over 512 MB, as in a step of a model), on the Llama-shaped layers:
-//  * up to 32 tokens the weight-streaming kernel for a few dozen tokens (K = N = 4096: 11 against
-//    14 us for the tiled kernel), except on layers with a long K when the caller brings the
-//    scratch that lets the tiled kernel split K over blocks (K = 14336, N = 4096: 20 against 27 us),
-//    and on layers so wide that blocks of 32 x 128 fill the chip (K = 4096, N = 28672: 17 against
-//    18 us; K = 8192, N = 57344: 53-57 against 59-62 us);
-//  * from 33 tokens the tiled kernel with its small block shapes (K = N = 4096 at 64 tokens: 14.5
-//    against 15.4 us; K = 4096, N = 28672: 21 against 25 us; K = 8192, N = 57344: 67 against 81 us),
-//    except where its K loop is long, cannot be split for want of scratch, and the grid of 64 x 128
-//    tiles leaves CUs empty (K = 14336, N = 4096: 37 us for the streaming kernel, 50 us tiled).
+// The library's choice of kernel.  Up to 16 tokens the decode path.  From 17 on the tiles cut along K where the
+// grid is small enough for them (slices_pay, whose comment has the measurements: K = N = 4096 up to 128 tokens).  What is
+// left of 17 to 64 tokens lies between the two paths the workload names.  Measured with every launch reading
+// its weights from HBM (copies of the layer rotating over 512 MB, as in a step of a model), on the Llama-shaped layers:
+//  * up to 32 tokens the weight-streaming kernel for a few dozen tokens (K = N = 8192: 18.1-18.9 against
+//    18.5-19.9 us for the tiled kernel), except on layers with a long K when the caller brings the
+//    scratch that lets the tiled kernel split K over blocks (K = 14336, N = 4096: 17-19 against 27 us),
+//    and on layers so wide that blocks of 32 x 128 fill the chip (K = 4096, N = 28672: 16-17 against
+//    17-18 us; K = 8192, N = 57344: 53-56 against 59-62 us);
+//  * from 33 tokens the tiled kernel with its small block shapes (K = 4096, N = 28672 at 64 tokens: 20
+//    against 25 us; K = 8192, N = 57344: 65 against 81 us), except where its K loop is long, cannot be split
+//    for want of scratch, and the grid of 64 x 128 tiles leaves CUs empty (measured on K = 14336, N = 4096, before the
+//    tiles cut along K took that shape: 37 us for the streaming kernel, 50 us tiled; left to it is K = 8192, N = 10240).
 int auto_path(const mixllm_desc &d, const LinearParams &p)
 {
     if (d.M <= 16) return MIXLLM_PATH_DECODE;

@@ -430,7 +430,7 @@ static __device__ __forceinline__ void prefill_block(const LinearParams &p, int 
 #pragma unroll
             for (int i = 0; i < 4; ++i) acc[mt][4 * j + i] = __builtin_fmaf((float)P[4 * j + i], sw, acc[mt][4 * j + i]);
         } else {
-            // per-(token, group) activation scales: the products of both scales, formed by the matrix pipe (see below)
+            // per-(token, group) activation scales: the products of both scales, formed by the matrix pipe (see above)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 acc[mt][4 * j + i] = __builtin_fmaf((float)P[4 * j + i], scale_products[mt % NB][4 * j + i], acc[mt][4 * j + i]);
@@ -934,16 +934,17 @@ __global__ __launch_bounds__(C::THREADS, MINW) void linear_prefill_kernel(Linear
 #endif
 }
 
-// Grids of up to two tiles of 32 x 32 per CU.  There the tiled kernel is a race of serial chains: K = N = 4096 at 48 tokens
+// Grids of up to about two tiles of 32 x 32 per CU (slices_pay).  There the tiled kernel is a race of serial chains: K = N = 4096 at 48 tokens
 // is 72 blocks of 32 x 128 on 256 CUs, each of them 32 groups of 0.3 us with one wave on a SIMD.  Here a block is one
 // tile of 32 tokens x 32 channels and its four waves take a quarter of K each (whole groups of 4 quantization groups),
 // with an activation tile of its own in LDS, the pipeline of prefill_block and no barrier in it; the quarters' sums meet
 // in LDS in a fixed order.  A quarter of the chain on four times the CUs, for four times the activation traffic, which
 // comes from the L2s: that traffic is what a step of four groups (24 KB a CU) then waits for, 0.5 us.  Measured from a
-// graph, weights from HBM, against the kernel that took the shape before: K = N = 4096 at 20 / 48 / 96 / 128 tokens
-// 10.8 / 13.6 / 13.8 / 13.7 -> 7.7 / 8.5 / 11.1 / 12.5 us; N = 6144 at 32 / 64 tokens 11.1 / 14.1 -> 8.4 / 11.5; K = N =
-// 8192 at 64 tokens 25.2 -> 21.7; K = 4096, N = 1024 at 300 tokens 12.1 -> 8.3.  Eight waves a block (two to a SIMD): 12.1
-// where four take 8.4; tiles of 64 tokens: 9.9.
+// graph, weights from HBM, against the kernel that takes the shape otherwise: K = N = 4096 at 20 / 48 / 96 / 128 tokens
+// 10.8 / 13.5 / 13.7 / 13.6 -> 7.8 / 8.9 / 11.3 / 12.8 us, with scales per group on both sides 12.7 / 16.8 / 17.1 / 16.9 -> 8.3 /
+// 9.8 / 12.3 / 14.6; N = 6144 at 32 / 64 tokens 11.2 / 13.9 -> 8.4 / 11.5; K = N = 8192 at 64 tokens 24.7 -> 21.7; K = 4096,
+// N = 1024 at 300 tokens 12.9 -> 9.7.  Eight waves a block (two to a SIMD): 12.1 where four take 8.4.  Tiles of 64
+// tokens were tried up to 48 tokens only, where most of the second half is padding (9.9 against 8.4).
 constexpr int SLICES = 4;
 constexpr size_t slices_lds_bytes(bool act_pt)
 {
@@ -1099,8 +1100,8 @@ static int launch_shape(const LinearParams &p, hipStream_t st)
         return (int)hipErrorInvalidValue;
     }
     // Per-(token, group) activation scales: built for one and two token tiles per wave.  With four
-    // the kernel needs more than 256 registers (the scale reads from LDS and the extra multiply
-    // come on top of 235), and a kernel with hand-issued loads must not spill.
+    // the kernel needs more than 256 registers (the 32 of the scale products come on top of 222), and a
+    // kernel with hand-issued loads must not spill.
     if constexpr (C::TM <= 2) {
         if (p.w8_per_channel)
             return p.S ? go(linear_prefill_kernel<C, MINW, 2, false, true>, true) : go(linear_prefill_kernel<C, MINW, 0, false, true>, true);
